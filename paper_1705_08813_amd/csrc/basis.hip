@@ -167,6 +167,76 @@ void fill_poisson_ops(int np, int nq, double* out) {
   for (int i = 0; i < o.n; ++i) f[i] = (float)out[i];
 }
 
+void fill_lin_ops(int np, double* out) {
+  const LinOps o = lin_ops(np);
+  // long double throughout: the tables are rounded once
+  using R = long double;
+  double gl[kMaxP], g[kMaxQ], w[kMaxQ], v[kMaxP], d[kMaxP];
+  lobatto_nodes(np, gl);
+  gauss_rule(np, g, w);  // exact for the products of two basis functions
+  R M[kMaxP][kMaxP] = {}, K[kMaxP][kMaxP] = {}, C[kMaxP][kMaxP] = {}, I[kMaxP][kMaxP] = {};
+  for (int q = 0; q < np; ++q) {
+    lagrange_eval(gl, np, g[q], v, d);
+    for (int i = 0; i < np; ++i)
+      for (int j = 0; j < np; ++j) {
+        M[i][j] += (R)w[q] * v[i] * v[j];
+        K[i][j] += (R)w[q] * d[i] * d[j];
+        C[i][j] += (R)w[q] * d[i] * v[j];
+      }
+  }
+  {  // I = M^{-1} by Gauss-Jordan elimination (M is symmetric positive definite)
+    R T[kMaxP][kMaxP];
+    for (int i = 0; i < np; ++i)
+      for (int j = 0; j < np; ++j) {
+        T[i][j] = M[i][j];
+        I[i][j] = i == j;
+      }
+    for (int c = 0; c < np; ++c) {
+      const R p = 1 / T[c][c];
+      for (int j = 0; j < np; ++j) {
+        T[c][j] *= p;
+        I[c][j] *= p;
+      }
+      for (int i = 0; i < np; ++i) {
+        if (i == c) continue;
+        const R f = T[i][c];
+        for (int j = 0; j < np; ++j) {
+          T[i][j] -= f * T[c][j];
+          I[i][j] -= f * I[c][j];
+        }
+      }
+    }
+  }
+  double nd0[kMaxP], nd1[kMaxP];
+  lagrange_eval(gl, np, 0.0, v, nd0);
+  lagrange_eval(gl, np, 1.0, v, nd1);
+  for (int i = 0; i < np; ++i) {
+    lagrange_eval(gl, np, gl[i], v, d);
+    R a0 = 0, a1 = 0;
+    for (int j = 0; j < np; ++j) {
+      out[o.M + i * np + j] = (double)M[i][j];
+      out[o.Dn + i * np + j] = d[j];
+      R a = 0, e = 0;
+      for (int k = 0; k < np; ++k) {
+        a += I[i][k] * K[k][j];
+        e += I[i][k] * C[k][j];
+      }
+      out[o.A + i * np + j] = (double)a;
+      out[o.E + i * np + j] = (double)e;
+      a0 += I[i][j] * nd0[j];
+      a1 += I[i][j] * nd1[j];
+    }
+    out[o.l0 + i] = (double)I[i][0];
+    out[o.l1 + i] = (double)I[i][np - 1];
+    out[o.g0 + i] = (double)a0;
+    out[o.g1 + i] = (double)a1;
+    out[o.nd0 + i] = nd0[i];
+    out[o.nd1 + i] = nd1[i];
+  }
+  float* f = reinterpret_cast<float*>(out + o.f32);
+  for (int i = 0; i < o.n; ++i) f[i] = (float)out[i];
+}
+
 // van Driest's law at the support points y+_i = 0, 5, 11, 24, 59, 144, 361,
 // 946, 2517 (the locations of the paper's Table tab:psi): composite 12-point
 // Gauss-Legendre on unit panels up to 64, then panels of 10 % of the abscissa

@@ -96,6 +96,8 @@ __device__ __forceinline__ int find_seg(const SegArr<S, K>& a, int64_t bid) {
 
 // Host side: descriptors of one mesh level, workgroup counts, batched launchers.
 MeshDev poisson_meshdev(const dg_mesh* m, int l);
+// mesh arguments of the velocity kernels
+MeshDev velocity_meshdev(const dg_mesh* m);
 Tr mg_transfer_geometry(const dg_mesh* m, int l);
 int poisson_cells_per_block(int np);
 // the transfer kernel family a level pair uses and its coarse cells per workgroup

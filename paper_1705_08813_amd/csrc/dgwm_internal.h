@@ -71,6 +71,37 @@ __host__ __device__ constexpr PoiOps poi_ops(int np) {
   return o;
 }
 
+// 1-D operators of the velocity basis on the reference cell, stored behind
+// the velocity tables: M the mass matrix, Dn[k][j] = N_j'(x_k) (the derivative
+// in nodal form, M Dn = int N_i N_j'), A = M^{-1} K with the stiffness matrix
+// K, E = M^{-1} C with C_ij = int N_i' N_j, l0/l1 = M^{-1} N(0), M^{-1} N(1),
+// g0/g1 = M^{-1} N'(0), M^{-1} N'(1), nd0/nd1 = N'(0), N'(1); in double, then
+// the same entries in float.
+struct LinOps {
+  int M, Dn, A, E, l0, l1, g0, g1, nd0, nd1, n;
+  int f32;   // offset (in doubles) of the float block
+  int size;  // doubles in total
+};
+__host__ __device__ constexpr LinOps lin_ops(int np) {
+  LinOps o{};
+  o.M = 0;
+  o.Dn = np * np;
+  o.A = 2 * np * np;
+  o.E = 3 * np * np;
+  o.l0 = 4 * np * np;
+  o.l1 = o.l0 + np;
+  o.g0 = o.l1 + np;
+  o.g1 = o.g0 + np;
+  o.nd0 = o.g1 + np;
+  o.nd1 = o.nd0 + np;
+  o.n = o.nd1 + np;
+  o.f32 = o.n;
+  o.size = o.n + (o.n + 1) / 2;
+  return o;
+}
+// offset of that block from the start of the velocity tables
+__host__ __device__ constexpr int lin_offset(int np, int nq, int nqy) { return tab_layout(np, nq, nqy).size + nq + nqy; }
+
 // Points of the enrichment tables of one enriched cell: the volume rule
 // nq x nqy x nq, then the six faces f = 2d + s in order.  Face (d,s) has
 // tangential directions t1 < t2; its points are q1 + Q1 q2 with Q = nqy for
@@ -88,6 +119,7 @@ __host__ __device__ constexpr int psi_points(int nq, int nqy) { return psi_face_
 // Host-side 1-D tables (basis.cpp).
 void fill_tables(int np, int nq, int nqy, double* out);
 void fill_poisson_ops(int np, int nq, double* out);  // poi_ops(np).size doubles
+void fill_lin_ops(int np, double* out);              // lin_ops(np).size doubles
 void gauss_rule(int n, double* x, double* w);
 void lobatto_nodes(int n, double* x);
 
@@ -229,7 +261,12 @@ int launch_velocity(const dg_mesh* m, dg_prec prec, const void* u, void* r, hipS
 // eddy viscosity nu_t at every point of the psi tables from the enrichment
 // coefficients of u, and out = A u for the multiscale viscous operator
 int launch_eddy_viscosity(const dg_mesh* m, const double* u, double c_des, double beta, double* nut, hipStream_t s);
-int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double* u, double* out, hipStream_t s);
+// inverse_mass: out = M^{-1} A u, one pass where the operator allows it
+int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double* u, double* out, hipStream_t s,
+                              bool inverse_mass = false);
+// the same operator on the layers [lo, lo + nl) without enriched neighbours, from 1-D operators (kern_linear.hip)
+int launch_viscous_regular(const dg_mesh* m, const double* u, double* out, int lo, int nl, bool inverse_mass,
+                           hipStream_t s);
 // div-div penalty: tau_D per cell from u (tau = true, out: ncell doubles) or out = D u with tau_d
 int launch_divdiv(const dg_mesh* m, bool tau, const double* u, const double* tau_d, double dt_over_cr, double* out,
                   hipStream_t s);
@@ -254,6 +291,14 @@ int launch_projection_step(const dg_mesh* m, const double* tau_d, const double* 
                            double* x, hipStream_t s);
 // x = M^{-1} r with the velocity mass matrix (flat meshes; x may be r)
 int launch_inverse_mass(const dg_mesh* m, const double* r, double* x, hipStream_t s);
+// the same on the nl layers lo, lo + step, ... (regular cells) and the enriched cells only
+int launch_inverse_mass_layers(const dg_mesh* m, const double* r, double* x, int lo, int nl, int step, hipStream_t s);
+// layers of cells without enrichment [lo, lo + nl); of these, the ones without an enriched neighbour
+// [ilo, ilo + inl), and the others: xnl layers from xlo, xstep apart
+struct RegularLayers {
+  int lo, nl, ilo, inl, xlo, xnl, xstep;
+};
+RegularLayers regular_layers(const dg_mesh* m);
 // vorticity right-hand side b(v) = (v, curl u)_e and the wall term of the
 // pressure Neumann data, added into rhs (kern_step.hip)
 int launch_vorticity_rhs(const dg_mesh* m, const double* u, double* b, hipStream_t s);

@@ -268,7 +268,8 @@ struct Gm {
   double* v(int k) const { return V + k * stride; }
   // y = K x = M^{-1} A x  (y != x), A the multiscale viscous operator or, with tau_d, the div-div penalty
   int apply_k(const double* x, double* y) {
-    int rc = tau_d ? launch_divdiv(m, false, x, tau_d, 0.0, y, s) : launch_viscous_multiscale(m, nut, x, y, s);
+    if (!tau_d) return launch_viscous_multiscale(m, nut, x, y, s, true);
+    int rc = launch_divdiv(m, false, x, tau_d, 0.0, y, s);
     if (!rc) rc = launch_inverse_mass(m, y, y, s);
     return rc;
   }

@@ -481,7 +481,8 @@ constexpr int kImThreads = 64;
 //   x~_c = (r~_c - a . r_bar_c) / (|det J| (r_psi, r_psi)),
 //   x_bar_c = |det J|^{-1} K^{-1} r_bar_c - a x~_c.
 template <int NP, bool ENR, int LE = 1>
-__global__ __launch_bounds__(kImThreads) void invmass_kernel(const InvMassArgs A, int layer_lo, int nlayers) {
+__global__ __launch_bounds__(kImThreads) void invmass_kernel(const InvMassArgs A, int layer_lo, int nlayers,
+                                                             int layer_step) {
   constexpr int NP2 = NP * NP, NP3 = NP2 * NP;
   __shared__ double u[3 * NP3];
   __shared__ double sa[ENR ? LE * NP3 : 1];
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(kImThreads) void invmass_kernel(const InvMassArgs A
   } else {
     const int ex = (int)(b % A.nx);
     const int64_t t0 = b / A.nx;
-    ey = layer_lo + (int)(t0 % nlayers);
+    ey = layer_lo + (int)(t0 % nlayers) * layer_step;
     e = ex + (int64_t)A.nx * (ey + (int64_t)A.ny * (t0 / nlayers));
   }
   const double* re = A.r + e * 3 * NP3;
@@ -1027,25 +1028,26 @@ int ensure_psi_poly(const dg_mesh* m, const InvMassArgs& A, hipStream_t s) {
 
 int launch_inverse_mass(const dg_mesh* m, const double* r, double* x, hipStream_t s) {
   if (m->curved) return launch_inverse_mass_curved(m, r, x, s);
+  const RegularLayers L = regular_layers(m);
+  return launch_inverse_mass_layers(m, r, x, L.lo, L.nl, 1, s);
+}
+
+int launch_inverse_mass_layers(const dg_mesh* m, const double* r, double* x, int lo, int nl, int step, hipStream_t s) {
   const InvMassArgs A = invmass_args(m, r, x);
   const int rc0 = ensure_psi_poly(m, A, s);
   if (rc0) return rc0;
-  // regular layers: all but the enriched wall-adjacent ones
-  const int lo = (m->P.fully_periodic || m->lower_slot < 0) ? 0 : 1;
-  const int hi = (m->P.fully_periodic || m->upper_slot < 0) ? m->P.ny - 1 : m->P.ny - 2;
-  const int nl = hi - lo + 1;
   const int64_t nreg = nl > 0 ? (int64_t)m->P.nx * nl * m->P.nz : 0;
 #define X(p)                                                                                                 \
   if (m->np_u == p) {                                                                                        \
     if (nreg > 0) {                                                                                          \
-      hipLaunchKernelGGL((invmass_kernel<p, false>), dim3((unsigned)nreg), dim3(kImThreads), 0, s, A, lo, nl); \
+      hipLaunchKernelGGL((invmass_kernel<p, false>), dim3((unsigned)nreg), dim3(kImThreads), 0, s, A, lo, nl, step); \
       const int rc = check_hip(hipGetLastError(), "inverse mass kernel launch");                             \
       if (rc) return rc;                                                                                     \
     }                                                                                                        \
     if (m->nenr > 0 && m->nle == 8)                                                                          \
-      hipLaunchKernelGGL((invmass_kernel<p, true, 8>), dim3((unsigned)m->nenr), dim3(kImThreads), 0, s, A, 0, 0); \
+      hipLaunchKernelGGL((invmass_kernel<p, true, 8>), dim3((unsigned)m->nenr), dim3(kImThreads), 0, s, A, 0, 0, 1); \
     else if (m->nenr > 0)                                                                                    \
-      hipLaunchKernelGGL((invmass_kernel<p, true>), dim3((unsigned)m->nenr), dim3(kImThreads), 0, s, A, 0, 0); \
+      hipLaunchKernelGGL((invmass_kernel<p, true>), dim3((unsigned)m->nenr), dim3(kImThreads), 0, s, A, 0, 0, 1); \
     return check_hip(hipGetLastError(), "inverse mass kernel launch");                                       \
   }
   X(3) X(4) X(5) X(6)

@@ -16,7 +16,7 @@
 // grad psi tables.
 #include <cstring>
 
-#include "kern_common.h"
+#include "batch.h"
 
 namespace dgwm {
 
@@ -1553,11 +1553,11 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
   }
 }
 
-// One cell: block-local index b within its launch (regular cells: layer range
-// [layer_lo, layer_lo + nlayers); enriched cells: the enriched index).
+// One cell: block-local index b within its launch (regular cells: the layers
+// layer_lo + layer_step [0, nlayers); enriched cells: the enriched index).
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, bool MS = false, int LE = 1>
 __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __restrict__ u, T* __restrict__ r, int b,
-                                                 int layer_lo, int nlayers) {
+                                                 int layer_lo, int nlayers, int layer_step = 1) {
   static_assert(LE == 1 || (LE == 8 && !CURVED), "degree-1 weights: flat cells");
   using Sh = VelShape<T, NP, NQ, NQY>;
   constexpr int NP3 = Sh::NP3, NPTS = Sh::NPTS;
@@ -1581,7 +1581,7 @@ __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __re
     ey = (slot == M.lower_slot) ? 0 : M.ny - 1;
     enr = b;
   } else {
-    ey = layer_lo + t0 % nlayers;
+    ey = layer_lo + (t0 % nlayers) * layer_step;
     ez = t0 / nlayers;
   }
   const int64_t e = ex + (int64_t)M.nx * (ey + (int64_t)M.ny * ez);
@@ -1927,11 +1927,12 @@ __global__ __launch_bounds__(256, (vel_wg_per_cu<T, NP, NQ, NQY, ENR, CURVED, LE
 // its viscous-only mode.
 template <int NP, int NQ, int NQY, bool ENR, int LE = 1>
 __global__ __launch_bounds__(256, (LE == 8 && ENR) ? 2 : 3) void visc_ms_kernel(const MeshDev M, const double* __restrict__ u,
-                                                         double* __restrict__ r, int layer_lo, int nlayers) {
+                                                         double* __restrict__ r, int layer_lo, int nlayers,
+                                                         int layer_step) {
   const int nb = gridDim.x, bid = blockIdx.x;
   const int q8 = nb >> 3, r8 = nb & 7, xcd = bid & 7, m8 = bid >> 3;
   const int blk = xcd * q8 + (xcd < r8 ? xcd : r8) + m8;
-  vel_cell_general<double, NP, NQ, NQY, ENR, false, true, LE>(M, u, r, blk, layer_lo, nlayers);
+  vel_cell_general<double, NP, NQ, NQY, ENR, false, true, LE>(M, u, r, blk, layer_lo, nlayers, layer_step);
 }
 
 // One mesh of a batched launch.
@@ -2007,7 +2008,9 @@ int launch_vel_l1_t(const dg_mesh* m, const MeshDev& M, const void* u, void* r, 
   return check_hip(hipGetLastError(), "velocity kernel launch");
 }
 
-MeshDev make_meshdev_u(const dg_mesh* m) {
+}  // namespace
+
+MeshDev velocity_meshdev(const dg_mesh* m) {
   MeshDev M{};
   M.nx = m->P.nx;
   M.ny = m->P.ny;
@@ -2039,8 +2042,6 @@ MeshDev make_meshdev_u(const dg_mesh* m) {
   return M;
 }
 
-}  // namespace
-
 // (np, nq, nq_wn) combinations compiled in.
 #define DG_VEL_COMBOS(X) \
   X(3, 4, 8)             \
@@ -2057,13 +2058,6 @@ MeshDev make_meshdev_u(const dg_mesh* m) {
   X(4, 4, 8)                \
   X(4, 5, 8)                \
   X(5, 7, 8)
-
-// Regular-layer range of a mesh (cells not in an enriched layer).
-static void regular_layers(const dg_mesh* m, int& lo, int& nl) {
-  lo = (m->P.fully_periodic || m->lower_slot < 0) ? 0 : 1;
-  const int hi = (m->P.fully_periodic || m->upper_slot < 0) ? m->P.ny - 1 : m->P.ny - 2;
-  nl = hi - lo + 1;
-}
 
 template <typename T, int NP, int NQ, int NQW, bool CURVED>
 static void launch_batch_group(const VelBatchItem* d_items_reg, const int64_t* d_pre_reg, int nreg, int64_t tot_reg,
@@ -2097,53 +2091,54 @@ bool velocity_l1_supported(int np, int nq, int nqy) {
 
 const char* velocity_l1_combos() { return "(3,4,8) (4,4,8) (4,5,8) (5,7,8)"; }
 
-template <int NP, int NQ, int NQW>
-static int launch_visc_ms_t(const dg_mesh* m, MeshDev M, const double* u, double* r, hipStream_t s) {
-  const int lo = (m->P.fully_periodic || m->lower_slot < 0) ? 0 : 1;
-  const int hi = (m->P.fully_periodic || m->upper_slot < 0) ? m->P.ny - 1 : m->P.ny - 2;
-  const int nl = hi - lo + 1;
-  if (nl > 0)
-    hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQ, false>), dim3((unsigned)((int64_t)m->P.nx * nl * m->P.nz)),
-                       dim3(256), 0, s, M, u, r, lo, nl);
+// Cells next to an enriched layer and enriched cells; the other cells take
+// launch_viscous_regular.
+template <int NP, int NQ, int NQW, int LE>
+static int launch_visc_ms_t(const dg_mesh* m, const MeshDev& M, const RegularLayers& L, const double* u, double* r,
+                            hipStream_t s) {
+  if (L.xnl > 0)
+    hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQ, false, LE>), dim3((unsigned)((int64_t)m->P.nx * L.xnl * m->P.nz)),
+                       dim3(256), 0, s, M, u, r, L.xlo, L.xnl, L.xstep);
   if (m->nenr > 0)
-    hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQW, true>), dim3((unsigned)m->nenr), dim3(256), 0, s, M, u, r, 0, 0);
+    hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQW, true, LE>), dim3((unsigned)m->nenr), dim3(256), 0, s, M, u, r, 0,
+                       0, 1);
   return check_hip(hipGetLastError(), "multiscale viscous kernel launch");
 }
 
-// Degree-1 enrichment weights: the regular cells read the 24 coefficients of
-// an enriched neighbour.
-template <int NP, int NQ, int NQW>
-static int launch_visc_ms_l1_t(const dg_mesh* m, MeshDev M, const double* u, double* r, hipStream_t s) {
-  const int lo = (m->P.fully_periodic || m->lower_slot < 0) ? 0 : 1;
-  const int hi = (m->P.fully_periodic || m->upper_slot < 0) ? m->P.ny - 1 : m->P.ny - 2;
-  const int nl = hi - lo + 1;
-  if (nl > 0)
-    hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQ, false, 8>), dim3((unsigned)((int64_t)m->P.nx * nl * m->P.nz)),
-                       dim3(256), 0, s, M, u, r, lo, nl);
-  hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQW, true, 8>), dim3((unsigned)m->nenr), dim3(256), 0, s, M, u, r, 0, 0);
-  return check_hip(hipGetLastError(), "multiscale viscous kernel launch");
-}
-
-int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double* u, double* out, hipStream_t s) {
-  MeshDev M = make_meshdev_u(m);
+int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double* u, double* out, hipStream_t s,
+                              bool inverse_mass) {
+  MeshDev M = velocity_meshdev(m);
   M.nut = nut;
+  const RegularLayers L = regular_layers(m);
+  int rc = launch_viscous_regular(m, u, out, L.ilo, L.inl, inverse_mass, s);
+  if (rc || m->nenr == 0) return rc;
   const int np = m->np_u, nq = m->P.nq_u, nqw = m->P.nq_wn;
-  if (m->nle != 1 && m->nenr > 0) {
-#define X(a, b, c) \
-  if (np == a && nq == b && nqw == c) return launch_visc_ms_l1_t<a, b, c>(m, M, u, out, s);
+  bool done = false;
+  if (m->nle != 1) {
+#define X(a, b, c)                           \
+  if (!done && np == a && nq == b && nqw == c) { \
+    rc = launch_visc_ms_t<a, b, c, 8>(m, M, L, u, out, s); \
+    done = true;                             \
+  }
     DG_VEL_L1_COMBOS(X)
 #undef X
-    return set_error(DG_ERR_UNSUPPORTED, "degree-1 enrichment weights: combination not compiled");
+    if (!done) return set_error(DG_ERR_UNSUPPORTED, "degree-1 enrichment weights: combination not compiled");
+  } else {
+#define X(a, b, c)                           \
+  if (!done && np == a && nq == b && nqw == c) { \
+    rc = launch_visc_ms_t<a, b, c, 1>(m, M, L, u, out, s); \
+    done = true;                             \
   }
-#define X(a, b, c)                                                        \
-  if (np == a && nq == b && (nqw == c || m->nenr == 0)) return launch_visc_ms_t<a, b, c>(m, M, u, out, s);
-  DG_VEL_COMBOS(X)
+    DG_VEL_COMBOS(X)
 #undef X
-  return set_error(DG_ERR_UNSUPPORTED, "velocity degree/quadrature combination not compiled");
+    if (!done) return set_error(DG_ERR_UNSUPPORTED, "velocity degree/quadrature combination not compiled");
+  }
+  if (!rc && inverse_mass) rc = launch_inverse_mass_layers(m, out, out, L.xlo, L.xnl, L.xstep, s);
+  return rc;
 }
 
 int launch_velocity(const dg_mesh* m, dg_prec prec, const void* u, void* r, hipStream_t s, bool convective_only) {
-  MeshDev M = make_meshdev_u(m);
+  MeshDev M = velocity_meshdev(m);
   if (convective_only) M.nu = 0.0;  // every viscous term carries a factor nu
   const int np = m->np_u, nq = m->P.nq_u, nqw = m->P.nq_wn;
   if (m->nle != 1 && m->nenr > 0) {
@@ -2260,12 +2255,12 @@ int launch_velocity_batched(const dg_mesh* const* meshes, int n, dg_prec prec, c
       for (int i = 0; i < n; ++i) {
         if (key_of[i] != g) continue;
         const dg_mesh* m = meshes[i];
-        int lo, nl;
-        regular_layers(m, lo, nl);
+        const RegularLayers RL = regular_layers(m);
+        const int lo = RL.lo, nl = RL.nl;
         const int64_t nb = cls == 0 ? (nl > 0 ? (int64_t)m->P.nx * nl * m->P.nz : 0) : m->nenr;
         if (nb == 0) continue;
         VelBatchItem it{};
-        it.M = make_meshdev_u(m);
+        it.M = velocity_meshdev(m);
         it.u = u[i];
         it.r = r[i];
         it.layer_lo = lo;
