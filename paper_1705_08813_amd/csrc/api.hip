@@ -154,7 +154,7 @@ WsLayout layout(const dg_mesh& m) {
   L.eta = o; o = up256(o + sizeof(double) * (m.P.ny + 1));
   L.hy = o; o = up256(o + sizeof(double) * 2 * m.P.ny);  // heights, then their reciprocals
   L.tab_u = o;
-  o = up256(o + sizeof(double) * (lin_offset(m.np_u, m.P.nq_u, m.P.nq_wn) + lin_ops(m.np_u).size));
+  o = up256(o + sizeof(double) * (mix_offset(m.np_u, m.P.nq_u, m.P.nq_wn) + mix_ops(m.np_u, m.np_p).size));
   L.tab_p = o;
   o = up256(o + sizeof(double) * (tab_layout(m.np_p, m.P.nq_p, m.P.nq_p).size + poi_ops(m.np_p).size));
   L.tau = o; o = up256(o + sizeof(double) * m.n_tau);
@@ -297,11 +297,12 @@ int dg_setup_mesh(const dg_mesh_params* params, const double* tau_w_host, void* 
     hy[P.ny + j] = 1.0 / hy[j];
   }
   const TabLayout Lu = tab_layout(m->np_u, P.nq_u, P.nq_wn);
-  std::vector<double> tu(lin_offset(m->np_u, P.nq_u, P.nq_wn) + lin_ops(m->np_u).size), tp(tab_layout(m->np_p, P.nq_p, P.nq_p).size + poi_ops(m->np_p).size);
+  std::vector<double> tu(mix_offset(m->np_u, P.nq_u, P.nq_wn) + mix_ops(m->np_u, m->np_p).size), tp(tab_layout(m->np_p, P.nq_p, P.nq_p).size + poi_ops(m->np_p).size);
   fill_tables(m->np_u, P.nq_u, P.nq_wn, tu.data());
   for (int q = 0; q < P.nq_u; ++q) tu[Lu.size + q] = tu[Lu.g + q];
   for (int q = 0; q < P.nq_wn; ++q) tu[Lu.size + P.nq_u + q] = tu[Lu.gy + q];
   fill_lin_ops(m->np_u, tu.data() + lin_offset(m->np_u, P.nq_u, P.nq_wn));
+  fill_mix_ops(m->np_u, m->np_p, tu.data() + mix_offset(m->np_u, P.nq_u, P.nq_wn));
   fill_tables(m->np_p, P.nq_p, P.nq_p, tp.data());
   fill_poisson_ops(m->np_p, P.nq_p, tp.data() + tab_layout(m->np_p, P.nq_p, P.nq_p).size);
   std::vector<double> tau(m->n_tau, 1.0);

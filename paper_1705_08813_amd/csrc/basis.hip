@@ -237,6 +237,30 @@ void fill_lin_ops(int np, double* out) {
   for (int i = 0; i < o.n; ++i) f[i] = (float)out[i];
 }
 
+void fill_mix_ops(int npu, int npp, double* out) {
+  const MixOps o = mix_ops(npu, npp);
+  const int nq = npu > npp ? npu : npp;  // exact for the products
+  double gu[kMaxP], gp[kMaxP], g[kMaxQ], w[kMaxQ], vu[kMaxP], du[kMaxP], vp[kMaxP], dp[kMaxP];
+  lobatto_nodes(npu, gu);
+  lobatto_nodes(npp, gp);
+  gauss_rule(nq, g, w);
+  for (int i = 0; i < npu; ++i)
+    for (int a = 0; a < npp; ++a) {
+      const double ends = (i == npu - 1 && a == npp - 1 ? 0.5 : 0.0) - (i == 0 && a == 0 ? 0.5 : 0.0);
+      long double m = 0, cu = 0, cp = 0;
+      for (int q = 0; q < nq; ++q) {
+        lagrange_eval(gu, npu, g[q], vu, du);
+        lagrange_eval(gp, npp, g[q], vp, dp);
+        m += (long double)w[q] * vu[i] * vp[a];
+        cu += (long double)w[q] * du[i] * vp[a];
+        cp += (long double)w[q] * dp[a] * vu[i];
+      }
+      out[o.Mup + i * npp + a] = (double)m;
+      out[o.Gu + i * npp + a] = (double)(ends - cu);
+      out[o.Gp + a * npu + i] = (double)(ends - cp);
+    }
+}
+
 // van Driest's law at the support points y+_i = 0, 5, 11, 24, 59, 144, 361,
 // 946, 2517 (the locations of the paper's Table tab:psi): composite 12-point
 // Gauss-Legendre on unit panels up to 64, then panels of 10 % of the abscissa

@@ -102,6 +102,17 @@ __host__ __device__ constexpr LinOps lin_ops(int np) {
 // offset of that block from the start of the velocity tables
 __host__ __device__ constexpr int lin_offset(int np, int nq, int nqy) { return tab_layout(np, nq, nqy).size + nq + nqy; }
 
+// 1-D operators between the velocity basis N (npu nodes) and the pressure
+// basis P (npp nodes), behind the block above:
+//   Mup[i][a] = int N_i P_a,
+//   Gu[i][a] = -int N_i' P_a + 1/2 [N_i P_a]_0^1   (gradient: own half of the central face average included),
+//   Gp[a][i] = -int P_a' N_i + 1/2 [P_a N_i]_0^1   (divergence).
+struct MixOps {
+  int Mup, Gu, Gp, size;
+};
+__host__ __device__ constexpr MixOps mix_ops(int npu, int npp) { return MixOps{0, npu * npp, 2 * npu * npp, 3 * npu * npp}; }
+__host__ __device__ constexpr int mix_offset(int np, int nq, int nqy) { return lin_offset(np, nq, nqy) + lin_ops(np).size; }
+
 // Points of the enrichment tables of one enriched cell: the volume rule
 // nq x nqy x nq, then the six faces f = 2d + s in order.  Face (d,s) has
 // tangential directions t1 < t2; its points are q1 + Q1 q2 with Q = nqy for
@@ -120,6 +131,7 @@ __host__ __device__ constexpr int psi_points(int nq, int nqy) { return psi_face_
 void fill_tables(int np, int nq, int nqy, double* out);
 void fill_poisson_ops(int np, int nq, double* out);  // poi_ops(np).size doubles
 void fill_lin_ops(int np, double* out);              // lin_ops(np).size doubles
+void fill_mix_ops(int npu, int npp, double* out);    // mix_ops(npu, npp).size doubles
 void gauss_rule(int n, double* x, double* w);
 void lobatto_nodes(int n, double* x);
 
@@ -302,6 +314,13 @@ RegularLayers regular_layers(const dg_mesh* m);
 // vorticity right-hand side b(v) = (v, curl u)_e and the wall term of the
 // pressure Neumann data, added into rhs (kern_step.hip)
 int launch_vorticity_rhs(const dg_mesh* m, const double* u, double* b, hipStream_t s);
+int launch_vorticity(const dg_mesh* m, const double* u, double* omega, hipStream_t s);  // M^{-1} of it
+// the same on cells without enrichment, layers [lo, lo + nl) (kern_linear.hip)
+int launch_vorticity_regular(const dg_mesh* m, const double* u, double* b, int lo, int nl, bool inverse_mass,
+                             hipStream_t s);
+// out = C u or P p on the layers [lo, lo + nl) without enrichment (C: without enriched neighbours)
+int launch_divgrad_regular(const dg_mesh* m, bool divergence, const double* in, double* out, int lo, int nl,
+                           hipStream_t s);
 int launch_pressure_neumann(const dg_mesh* m, int nh, const double* const* us, const double* const* oms,
                             const double* beta, const double* f, double* rhs, hipStream_t s);
 // Helmholtz step (helmholtz.hip): workspace bytes and the restarted GMRES solve

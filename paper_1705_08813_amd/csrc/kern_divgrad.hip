@@ -35,6 +35,7 @@ constexpr int kDgThreads = 256;
 
 struct DgArgs {
   int nx, ny, nz, lower_slot, upper_slot, nslots, psi_pts, fully_periodic;
+  int layer_step;          // regular cells: layers layer_lo + layer_step [0, nlayers)
   int psi_off[7];          // volume, then the six faces f = 2d + s
   int64_t ncell;
   double hx, hz;
@@ -70,7 +71,7 @@ __device__ __forceinline__ CellGeo cell_of_block(const DgArgs& A, int64_t b, int
     g.ez = (int)(t0 / A.nslots);
     g.ey = slot == A.lower_slot ? 0 : A.ny - 1;
   } else {
-    g.ey = layer_lo + (int)(t0 % nlayers);
+    g.ey = layer_lo + (int)(t0 % nlayers) * A.layer_step;
     g.ez = (int)(t0 / nlayers);
   }
   g.e = g.ex + (int64_t)A.nx * (g.ey + (int64_t)A.ny * g.ez);
@@ -488,23 +489,22 @@ int launch_divgrad(const dg_mesh* m, bool divergence, const double* in, double* 
   A.psi = m->psi;
   A.in = in;
   A.out = out;
-  const int lo = (m->P.fully_periodic || m->lower_slot < 0) ? 0 : 1;
-  const int hi = (m->P.fully_periodic || m->upper_slot < 0) ? m->P.ny - 1 : m->P.ny - 2;
-  const int nl = hi - lo + 1;
-  const int64_t nreg = nl > 0 ? (int64_t)m->P.nx * nl * m->P.nz : 0;
-  // without enriched cells only the regular kernels run and nq_wn is irrelevant
+  // cells without enrichment take the 1-D operators (launch_divgrad_regular); u of an enriched neighbour enters the
+  // divergence by quadrature, so the layers next to an enriched one keep the general kernel
+  const RegularLayers L = regular_layers(m);
+  A.layer_step = L.xstep;
+  const int64_t nreg = divergence ? (int64_t)m->P.nx * L.xnl * m->P.nz : 0;
+  // without enriched cells nq_wn is irrelevant
   const bool any_w = m->nenr == 0;
   const int nqw = m->P.nq_wn;
 #define LAUNCH(KER, pu, pp, q, w, ENRV, LEV, grid, lo_, nl_)                                            \
   hipLaunchKernelGGL((KER<pu, pp, q, w, ENRV, LEV>), dim3((unsigned)(grid)), dim3(kDgThreads), 0, s, A, lo_, nl_)
 #define RUN(LEV, pu, pp, q, w)                                                                           \
   {                                                                                                      \
-    if (nreg > 0) {                                                                                      \
-      if (divergence) LAUNCH(divergence_kernel, pu, pp, q, q, false, LEV, nreg, lo, nl);                  \
-      else LAUNCH(gradient_kernel, pu, pp, q, q, false, LEV, nreg, lo, nl);                               \
-      const int rc = check_hip(hipGetLastError(), "divergence/gradient kernel launch");                  \
-      if (rc) return rc;                                                                                 \
-    }                                                                                                    \
+    int rc = divergence ? launch_divgrad_regular(m, true, in, out, L.ilo, L.inl, s)                      \
+                        : launch_divgrad_regular(m, false, in, out, L.lo, L.nl, s);                      \
+    if (rc) return rc;                                                                                   \
+    if (nreg > 0) LAUNCH(divergence_kernel, pu, pp, q, q, false, LEV, nreg, L.xlo, L.xnl);                \
     if (m->nenr > 0) {                                                                                   \
       if (divergence) LAUNCH(divergence_kernel, pu, pp, q, w, true, LEV, m->nenr, 0, 0);                  \
       else LAUNCH(gradient_kernel, pu, pp, q, w, true, LEV, m->nenr, 0, 0);                               \

@@ -326,6 +326,414 @@ __global__ __launch_bounds__(256) void viscous_regular_kernel(const MeshDev M, i
                                   layer_lo, nlayers);
 }
 
+// Vorticity right-hand side b(v) = (v, curl u)_e in nodal form: curl u is a
+// polynomial of the cell's space, so b = |J| (M x M x M) curl u with the nodal
+// derivatives Dn u / h; MINV stops at M^{-1} b = curl u itself.
+// Thread (row r, line) takes d_{d1} u_{d2} of its row along d1, then
+// d_{d2} u_{d1} along d2 (d1 < d2 the other two directions) together with
+// the first mass sweep.  Bound by the read of u and the write of b: 83 us for
+// the 61,440 such cells of the 64 x 32 x 32 mesh, k = 4 (4.4 TB/s; 2713 us with
+// direct sums over the basis at the Gauss points).
+template <int NP, bool MINV>
+__global__ __launch_bounds__(256) void vorticity_regular_kernel(const MeshDev M, int lin_off,
+                                                                const double* __restrict__ u, double* __restrict__ out,
+                                                                int ncells, int layer_lo, int nlayers) {
+  using Sh = SepShape<NP>;
+  constexpr int NP2 = Sh::NP2, NP3 = Sh::NP3, CB = Sh::CB;
+  constexpr LinOps O = lin_ops(NP);
+  __shared__ double s_u[CB * 3 * Sh::SC];
+  __shared__ double s_r[CB * 3 * Sh::SC];
+  const double* ops = M.tab + lin_off;
+  const int tid = threadIdx.x, first = xcd_block(gridDim.x, blockIdx.x) * CB;
+  const int cell = tid / Sh::TPC, t = tid - cell * Sh::TPC;
+  const int r = t / NP2, k = t - r * NP2;
+  const int a = k % NP, b = k / NP;
+  const bool live = cell < CB && first + cell < ncells;
+  double* su = s_u + cell * 3 * Sh::SC;
+  double* sr = s_r + cell * 3 * Sh::SC + r * Sh::SC;
+  const int d1 = r == 0 ? 1 : 0, d2 = r == 2 ? 1 : 2;
+  // curl_r = sg (d_{d1} u_{d2} - d_{d2} u_{d1}), sg = -1 for r = y
+  const double sg = r == 1 ? -1.0 : 1.0;
+  double x[NP], ih[3] = {0, 0, 0};
+  int64_t e = 0;
+  auto load = [&](const double* p, int st) {
+#pragma unroll
+    for (int l = 0; l < NP; ++l) x[l] = p[l * st];
+  };
+  auto dot = [&](int tab, int l) {
+    double acc = 0;
+#pragma unroll
+    for (int m = 0; m < NP; ++m) acc += ops[tab + l * NP + m] * x[m];
+    return acc;
+  };
+  if (live) {
+    const int i = first + cell;
+    const int ex = i % M.nx, t0 = i / M.nx;
+    const int ey = layer_lo + t0 % nlayers, ez = t0 / nlayers;
+    e = ex + M.nx * (ey + (int64_t)M.ny * ez);
+    ih[0] = M.ihx;
+    ih[1] = M.ihy[ey];
+    ih[2] = M.ihz;
+    load(u + (e * 3 + r) * NP3 + NP * k, 1);
+#pragma unroll
+    for (int l = 0; l < NP; ++l) su[r * Sh::SC + Sh::SJ * k + l] = x[l];
+  }
+  __syncthreads();
+  const double f1 = sg * (d1 == 0 ? ih[0] : ih[1]), f2 = -sg * (d2 == 1 ? ih[1] : ih[2]);
+  int lb1, ls1, lb2, ls2;
+  lds_line<NP>(d1, a, b, lb1, ls1);
+  lds_line<NP>(d2, a, b, lb2, ls2);
+  if (live) {
+    load(su + d2 * Sh::SC + lb1, ls1);
+#pragma unroll
+    for (int l = 0; l < NP; ++l) sr[lb1 + l * ls1] = f1 * dot(O.Dn, l);
+  }
+  __syncthreads();
+  if (live) {
+    load(su + d1 * Sh::SC + lb2, ls2);
+    double v[NP];
+#pragma unroll
+    for (int l = 0; l < NP; ++l) v[l] = sr[lb2 + l * ls2] + f2 * dot(O.Dn, l);
+#pragma unroll
+    for (int l = 0; l < NP; ++l) x[l] = v[l];
+#pragma unroll
+    for (int l = 0; l < NP; ++l) sr[lb2 + l * ls2] = MINV ? x[l] : dot(O.M, l);
+  }
+  __syncthreads();
+  if (!MINV) {
+    // the other tangential direction: y for rows x and y, z for row z
+    int lb, ls;
+    lds_line<NP>(r == 2 ? 2 : 1, a, b, lb, ls);
+    if (live) {
+      load(sr + lb, ls);
+#pragma unroll
+      for (int l = 0; l < NP; ++l) sr[lb + l * ls] = dot(O.M, l);
+    }
+    __syncthreads();
+  }
+  if (live) {
+    load(sr + Sh::SJ * k, 1);
+    const double vol = 1.0 / (ih[0] * ih[1] * ih[2]);
+    double* o = out + (e * 3 + r) * NP3 + NP * k;
+#pragma unroll
+    for (int l = 0; l < NP; ++l) o[l] = MINV ? x[l] : vol * dot(O.M, l);
+  }
+}
+
+// Cells of a workgroup of the gradient and divergence kernels.
+template <int NU, int NPP>
+struct MixShape {
+  static constexpr int CB = NU <= 3 ? 8 : (NU <= 5 ? 4 : 2);
+};
+
+// Pressure gradient term on cells without enrichment, one component at a time
+// separable:  g_c = h_a h_b (G_c x M_a x M_b) p  with the 1-D operators of
+// mix_ops; the neighbours' halves of the central averages enter as one more
+// value at each end of the lines along c (walls: the cell's own end value).
+// The cell's pressure with its six neighbour layers is swept along z (lines
+// through the x and y neighbours' layers included), y and x.  Loops run over
+// the lines of all cells of the workgroup.  96 us for the 61,440 such cells of
+// the 64 x 32 x 32 mesh, k_u = 4, k_p = 3 (373 us by quadrature, 27 barrier
+// phases a cell): the write of g and five short phases bound it.
+template <int NU, int NPP>
+__global__ __launch_bounds__(256) void gradient_regular_kernel(const MeshDev M, int mix_off,
+                                                               const double* __restrict__ p, double* __restrict__ out,
+                                                               int ncells, int layer_lo, int nlayers) {
+  constexpr int CB = MixShape<NU, NPP>::CB, NP2 = NPP * NPP, NP3 = NP2 * NPP, NU2 = NU * NU, NU3 = NU2 * NU;
+  constexpr MixOps O = mix_ops(NU, NPP);
+  constexpr int LZ = NP2 + 4 * NPP;  // z lines with mass: (a, b), then x- and y-neighbour layers [S][tangential]
+  // P: pressure [node], then neighbour layers [D][S][NP2]; A: after z, mass [line][NU]; Gz: after z, gradient
+  constexpr int NPV = NP3 + 6 * NP2, NA = LZ * NU, NG = NP2 * NU;
+  // after y: x component on x in [-1, NPP] ext, y and z components
+  constexpr int NB = (NPP + 2) * NU2, NC = NPP * NU2;
+  constexpr int S1 = (NPV > NB + 2 * NC ? NPV : NB + 2 * NC), S2 = NA + NG;
+  __shared__ double s1[CB * S1];
+  __shared__ double s2[CB * S2];
+  __shared__ int s_e[CB * 7];  // cell, then its neighbours (walls: the cell itself, flagged below)
+  const double* ops = M.tab + mix_off;
+  const int tid = threadIdx.x, first = xcd_block(gridDim.x, blockIdx.x) * CB;
+  const int nc = ncells - first < CB ? ncells - first : CB;
+  if (tid < nc * 7) {
+    const int cell = tid / 7, f = tid - cell * 7 - 1;
+    const int i = first + cell;
+    const int ex = i % M.nx, t0 = i / M.nx;
+    const int ey = layer_lo + t0 % nlayers, ez = t0 / nlayers;
+    const int e = ex + M.nx * (ey + M.ny * ez);
+    s_e[tid] = f < 0 ? e : sep_nb(M, e, ex, ey, ez, f >> 1, f & 1);
+  }
+  __syncthreads();
+  for (int it = tid; it < nc * NPV; it += 256) {
+    const int cell = it / NPV, i = it - cell * NPV;
+    double v;
+    if (i < NP3) v = p[(int64_t)s_e[cell * 7] * NP3 + i];
+    else {
+      const int f = (i - NP3) / NP2, l = (i - NP3) - f * NP2, D = f >> 1, S = f & 1;
+      const int nb = s_e[cell * 7 + 1 + f];
+      // the neighbour's layer at the shared face; the cell's own on a wall
+      const int ld = (nb < 0) == (S == 1) ? NPP - 1 : 0;
+      const int l1 = l % NPP, l2 = l / NPP;
+      const int nd = D == 0 ? ld + NPP * l : (D == 1 ? l1 + NPP * (ld + NPP * l2) : l + NP2 * ld);
+      v = p[(int64_t)(nb < 0 ? s_e[cell * 7] : nb) * NP3 + nd];
+    }
+    s1[cell * S1 + i] = v;
+  }
+  __syncthreads();
+  // z: mass on the lines of the cell and of the x and y neighbour layers, gradient on the cell's
+  for (int it = tid; it < nc * (LZ + NP2); it += 256) {
+    const int cell = it / (LZ + NP2), i = it - cell * (LZ + NP2);
+    const double* P = s1 + cell * S1;
+    int base, st;
+    const bool grad = i >= LZ;
+    if (i < NP2 || grad) {
+      base = grad ? i - LZ : i;
+      st = NP2;
+    } else {  // layer of face (D, S), D = x: [y + NPP z], D = y: [x + NPP z]: tangential index l1, line along z
+      const int j = i - NP2, f = j / NPP;
+      base = NP3 + f * NP2 + (j - f * NPP);
+      st = NPP;
+    }
+    double x[NPP];
+#pragma unroll
+    for (int l = 0; l < NPP; ++l) x[l] = P[base + l * st];
+    double* o = s2 + cell * S2 + (grad ? NA + (i - LZ) * NU : i * NU);
+    if (grad) {
+      const double e0 = P[NP3 + 4 * NP2 + (i - LZ)], e1 = P[NP3 + 5 * NP2 + (i - LZ)];
+#pragma unroll
+      for (int q = 0; q < NU; ++q) {
+        double acc = q == 0 ? -0.5 * e0 : (q == NU - 1 ? 0.5 * e1 : 0.0);
+#pragma unroll
+        for (int l = 0; l < NPP; ++l) acc += ops[O.Gu + q * NPP + l] * x[l];
+        o[q] = acc;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NU; ++q) {
+        double acc = 0;
+#pragma unroll
+        for (int l = 0; l < NPP; ++l) acc += ops[O.Mup + q * NPP + l] * x[l];
+        o[q] = acc;
+      }
+    }
+  }
+  __syncthreads();
+  // y: mass for the x component (x neighbours' lines included) and the z component, gradient for the y one
+  constexpr int LY = (3 * NPP + 2) * NU;
+  for (int it = tid; it < nc * LY; it += 256) {
+    const int cell = it / LY, i = it - cell * LY;
+    const int line = i / NU, q = i - line * NU;  // q: z index
+    const double* A = s2 + cell * S2;
+    double* B = s1 + cell * S1;
+    double x[NPP];
+    if (line < NPP + 2) {
+      // x component: x = line, or the layers of the x neighbours (line NPP: S = 0, NPP + 1: S = 1)
+#pragma unroll
+      for (int l = 0; l < NPP; ++l)
+        x[l] = A[(line < NPP ? line + NPP * l : NP2 + (line - NPP) * NPP + l) * NU + q];
+#pragma unroll
+      for (int j = 0; j < NU; ++j) {
+        double acc = 0;
+#pragma unroll
+        for (int l = 0; l < NPP; ++l) acc += ops[O.Mup + j * NPP + l] * x[l];
+        B[line + (NPP + 2) * (j + NU * q)] = acc;
+      }
+    } else if (line < 2 * NPP + 2) {
+      const int xx = line - NPP - 2;
+#pragma unroll
+      for (int l = 0; l < NPP; ++l) x[l] = A[(xx + NPP * l) * NU + q];
+      const double e0 = A[(NP2 + 2 * NPP + xx) * NU + q], e1 = A[(NP2 + 3 * NPP + xx) * NU + q];
+#pragma unroll
+      for (int j = 0; j < NU; ++j) {
+        double acc = j == 0 ? -0.5 * e0 : (j == NU - 1 ? 0.5 * e1 : 0.0);
+#pragma unroll
+        for (int l = 0; l < NPP; ++l) acc += ops[O.Gu + j * NPP + l] * x[l];
+        B[NB + xx + NPP * (j + NU * q)] = acc;
+      }
+    } else {
+      const int xx = line - 2 * NPP - 2;
+#pragma unroll
+      for (int l = 0; l < NPP; ++l) x[l] = A[NA + (xx + NPP * l) * NU + q];
+#pragma unroll
+      for (int j = 0; j < NU; ++j) {
+        double acc = 0;
+#pragma unroll
+        for (int l = 0; l < NPP; ++l) acc += ops[O.Mup + j * NPP + l] * x[l];
+        B[NB + NC + xx + NPP * (j + NU * q)] = acc;
+      }
+    }
+  }
+  __syncthreads();
+  // x, and write
+  for (int it = tid; it < nc * 3 * NU2; it += 256) {
+    const int cell = it / (3 * NU2), i = it - cell * 3 * NU2;
+    const int c = i / NU2, k = i - c * NU2;
+    const int e = s_e[cell * 7];
+    const double hy = M.hy[(e / M.nx) % M.ny];
+    const double sc = c == 0 ? hy * M.hz : (c == 1 ? M.hx * M.hz : M.hx * hy);
+    const double* B = s1 + cell * S1 + (c == 0 ? (NPP + 2) * k : NB + (c - 1) * NC + NPP * k);
+    double x[NPP];
+#pragma unroll
+    for (int l = 0; l < NPP; ++l) x[l] = B[l];
+    const double e0 = c == 0 ? B[NPP] : 0.0, e1 = c == 0 ? B[NPP + 1] : 0.0;
+    double* o = out + ((int64_t)e * 3 + c) * NU3 + NU * k;
+    const double* tb = ops + (c == 0 ? O.Gu : O.Mup);
+#pragma unroll
+    for (int q = 0; q < NU; ++q) {
+      double acc = q == 0 ? -0.5 * e0 : (q == NU - 1 ? 0.5 * e1 : 0.0);
+#pragma unroll
+      for (int l = 0; l < NPP; ++l) acc += tb[q * NPP + l] * x[l];
+      o[q] = sc * acc;
+    }
+  }
+}
+
+// Velocity divergence term on cells without enrichment whose neighbours have
+// none either: the transposed sweeps, c = sum_c h_a h_b (Gp_c x M_a^T x M_b^T) u_c,
+// along x, y, z; component c brings the layers of its neighbours along c.
+// 116 us for 57,344 cells of the 64 x 32 x 32 mesh (by quadrature 547 us for
+// 61,440): the read of u and its neighbour layers bounds it.
+template <int NU, int NPP>
+__global__ __launch_bounds__(256) void divergence_regular_kernel(const MeshDev M, int mix_off,
+                                                                 const double* __restrict__ u,
+                                                                 double* __restrict__ out, int ncells, int layer_lo,
+                                                                 int nlayers) {
+  constexpr int CB = MixShape<NU, NPP>::CB, NP2 = NPP * NPP, NP3 = NP2 * NPP, NU2 = NU * NU, NU3 = NU2 * NU;
+  constexpr MixOps O = mix_ops(NU, NPP);
+  constexpr int NV = 3 * NU3 + 6 * NU2;  // u, then the neighbours' layers of their normal component [D][S][NU2]
+  // after x: u_x [NPP][NU y][NU z]; u_y with its layers [S] behind: lines (y, z), then [S][z]; u_z: (y, z), then [S][y]
+  constexpr int LX = 3 * NU2 + 4 * NU, NX = LX * NPP;
+  // after y: x and y parts together [NPP x][NPP y][NU z]; z part [NPP][NPP][NU], then [S][NPP][NPP]
+  constexpr int NY1 = NP2 * NU, NY2 = NP2 * (NU + 2);
+  constexpr int S1 = NV > NY1 + NY2 ? NV : NY1 + NY2;
+  __shared__ double s1[CB * S1];
+  __shared__ double s2[CB * NX];
+  __shared__ int s_e[CB * 7];
+  const double* ops = M.tab + mix_off;
+  const int tid = threadIdx.x, first = xcd_block(gridDim.x, blockIdx.x) * CB;
+  const int nc = ncells - first < CB ? ncells - first : CB;
+  if (tid < nc * 7) {
+    const int cell = tid / 7, f = tid - cell * 7 - 1;
+    const int i = first + cell;
+    const int ex = i % M.nx, t0 = i / M.nx;
+    const int ey = layer_lo + t0 % nlayers, ez = t0 / nlayers;
+    const int e = ex + M.nx * (ey + M.ny * ez);
+    s_e[tid] = f < 0 ? e : sep_nb(M, e, ex, ey, ez, f >> 1, f & 1);
+  }
+  __syncthreads();
+  for (int it = tid; it < nc * NV; it += 256) {
+    const int cell = it / NV, i = it - cell * NV;
+    double v;
+    if (i < 3 * NU3) v = u[(int64_t)s_e[cell * 7] * 3 * NU3 + i];
+    else {
+      const int f = (i - 3 * NU3) / NU2, l = (i - 3 * NU3) - f * NU2, D = f >> 1, S = f & 1;
+      const int nb = s_e[cell * 7 + 1 + f];
+      const int ld = (nb < 0) == (S == 1) ? NU - 1 : 0;
+      const int l1 = l % NU, l2 = l / NU;
+      const int nd = D == 0 ? ld + NU * l : (D == 1 ? l1 + NU * (ld + NU * l2) : l + NU2 * ld);
+      v = u[((int64_t)(nb < 0 ? s_e[cell * 7] : nb) * 3 + D) * NU3 + nd];
+    }
+    s1[cell * S1 + i] = v;
+  }
+  __syncthreads();
+  // x lines: gradient table for u_x, mass for u_y and u_z and the layers of the y and z neighbours
+  for (int it = tid; it < nc * LX; it += 256) {
+    const int cell = it / LX, i = it - cell * LX;
+    const double* V = s1 + cell * S1;
+    // lines [u_x: NU2 | u_y: NU2, then [S][z] | u_z: NU2, then [S][y]]
+    int base;
+    if (i < NU2) base = NU * i;
+    else if (i < 2 * NU2) base = NU3 + NU * (i - NU2);
+    else if (i < 2 * NU2 + 2 * NU) base = 3 * NU3 + 2 * NU2 + NU * (i - 2 * NU2);
+    else if (i < 3 * NU2 + 2 * NU) base = 2 * NU3 + NU * (i - 2 * NU2 - 2 * NU);
+    else base = 3 * NU3 + 4 * NU2 + NU * (i - 3 * NU2 - 2 * NU);
+    double x[NU];
+#pragma unroll
+    for (int l = 0; l < NU; ++l) x[l] = V[base + l];
+    double* o = s2 + cell * NX + i * NPP;
+    if (i < NU2) {
+      const double e0 = V[3 * NU3 + i], e1 = V[3 * NU3 + NU2 + i];
+#pragma unroll
+      for (int q = 0; q < NPP; ++q) {
+        double acc = q == 0 ? -0.5 * e0 : (q == NPP - 1 ? 0.5 * e1 : 0.0);
+#pragma unroll
+        for (int l = 0; l < NU; ++l) acc += ops[O.Gp + q * NU + l] * x[l];
+        o[q] = acc;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < NPP; ++q) {
+        double acc = 0;
+#pragma unroll
+        for (int l = 0; l < NU; ++l) acc += ops[O.Mup + l * NPP + q] * x[l];
+        o[q] = acc;
+      }
+    }
+  }
+  __syncthreads();
+  // y lines
+  constexpr int LY = NPP * NU + NPP * (NU + 2);
+  for (int it = tid; it < nc * LY; it += 256) {
+    const int cell = it / LY, i = it - cell * LY;
+    const double* X = s2 + cell * NX;
+    double* Y = s1 + cell * S1;
+    const int e = s_e[cell * 7];
+    const double hy = M.hy[(e / M.nx) % M.ny];
+    const int line = i / NPP, q = i - line * NPP;  // q: x index
+    double x[NU];
+    if (line < NU) {  // z = line: u_x with mass, u_y with the gradient table, their areas
+      const double* p = X + NU * line * NPP + q;
+      const double* py = X + (NU2 + NU * line) * NPP + q;
+      const double* pe = X + (2 * NU2 + line) * NPP + q;
+      double y[NU];
+#pragma unroll
+      for (int l = 0; l < NU; ++l) {
+        x[l] = hy * M.hz * p[l * NPP];
+        y[l] = M.hx * M.hz * py[l * NPP];
+      }
+      const double e0 = M.hx * M.hz * pe[0], e1 = M.hx * M.hz * pe[NU * NPP];
+#pragma unroll
+      for (int j = 0; j < NPP; ++j) {
+        double acc = j == 0 ? -0.5 * e0 : (j == NPP - 1 ? 0.5 * e1 : 0.0);
+#pragma unroll
+        for (int l = 0; l < NU; ++l) acc += ops[O.Mup + l * NPP + j] * x[l] + ops[O.Gp + j * NU + l] * y[l];
+        Y[q + NPP * (j + NPP * line)] = acc;
+      }
+    } else {
+      const int z = line - NU;  // < NU: the cell's z, else the z neighbours' layers
+      const double* p = X + (2 * NU2 + 2 * NU + NU * z) * NPP + q;
+#pragma unroll
+      for (int l = 0; l < NU; ++l) x[l] = M.hx * hy * p[l * NPP];
+#pragma unroll
+      for (int j = 0; j < NPP; ++j) {
+        double acc = 0;
+#pragma unroll
+        for (int l = 0; l < NU; ++l) acc += ops[O.Mup + l * NPP + j] * x[l];
+        Y[NY1 + q + NPP * (j + NPP * z)] = acc;
+      }
+    }
+  }
+  __syncthreads();
+  // z lines, and write
+  for (int it = tid; it < nc * NP2; it += 256) {
+    const int cell = it / NP2, k = it - cell * NP2;
+    const double* Y = s1 + cell * S1 + k;
+    double x[NU], y[NU];
+#pragma unroll
+    for (int l = 0; l < NU; ++l) {
+      x[l] = Y[NP2 * l];
+      y[l] = Y[NY1 + NP2 * l];
+    }
+    const double e0 = Y[NY1 + NP2 * NU], e1 = Y[NY1 + NP2 * (NU + 1)];
+    double* o = out + (int64_t)s_e[cell * 7] * NP3 + k;
+#pragma unroll
+    for (int q = 0; q < NPP; ++q) {
+      double acc = q == 0 ? -0.5 * e0 : (q == NPP - 1 ? 0.5 * e1 : 0.0);
+#pragma unroll
+      for (int l = 0; l < NU; ++l) acc += ops[O.Mup + l * NPP + q] * x[l] + ops[O.Gp + q * NU + l] * y[l];
+      o[q * NP2] = acc;
+    }
+  }
+}
+
 }  // namespace
 
 RegularLayers regular_layers(const dg_mesh* m) {
@@ -375,6 +783,50 @@ int launch_viscous_regular(const dg_mesh* m, const double* u, double* out, int l
   X(3) X(4) X(5) X(6)
 #undef X
   return set_error(DG_ERR_UNSUPPORTED, "viscous operator: degree not compiled");
+}
+
+int launch_vorticity_regular(const dg_mesh* m, const double* u, double* b, int lo, int nl, bool inverse_mass,
+                             hipStream_t s) {
+  if (nl <= 0) return DG_OK;
+  const MeshDev M = velocity_meshdev(m);
+  const int off = lin_offset(m->np_u, m->P.nq_u, m->P.nq_wn);
+  const int64_t nc = (int64_t)m->P.nx * nl * m->P.nz;
+#define X(p)                                                                                                        \
+  if (m->np_u == p) {                                                                                               \
+    const unsigned nb = (unsigned)((nc + SepShape<p>::CB - 1) / SepShape<p>::CB);                                   \
+    if (inverse_mass)                                                                                               \
+      hipLaunchKernelGGL((vorticity_regular_kernel<p, true>), dim3(nb), dim3(256), 0, s, M, off, u, b, (int)nc, lo,  \
+                         nl);                                                                                       \
+    else                                                                                                            \
+      hipLaunchKernelGGL((vorticity_regular_kernel<p, false>), dim3(nb), dim3(256), 0, s, M, off, u, b, (int)nc, lo, \
+                         nl);                                                                                       \
+    return check_hip(hipGetLastError(), "vorticity kernel launch");                                                 \
+  }
+  X(3) X(4) X(5) X(6)
+#undef X
+  return set_error(DG_ERR_UNSUPPORTED, "vorticity: degree not compiled");
+}
+
+int launch_divgrad_regular(const dg_mesh* m, bool divergence, const double* in, double* out, int lo, int nl,
+                           hipStream_t s) {
+  if (nl <= 0) return DG_OK;
+  const MeshDev M = velocity_meshdev(m);
+  const int off = mix_offset(m->np_u, m->P.nq_u, m->P.nq_wn);
+  const int64_t nc = (int64_t)m->P.nx * nl * m->P.nz;
+#define X(p, q)                                                                                                      \
+  if (m->np_u == p && m->np_p == q) {                                                                                \
+    const unsigned nb = (unsigned)((nc + MixShape<p, q>::CB - 1) / MixShape<p, q>::CB);                              \
+    if (divergence)                                                                                                  \
+      hipLaunchKernelGGL((divergence_regular_kernel<p, q>), dim3(nb), dim3(256), 0, s, M, off, in, out, (int)nc, lo, \
+                         nl);                                                                                        \
+    else                                                                                                             \
+      hipLaunchKernelGGL((gradient_regular_kernel<p, q>), dim3(nb), dim3(256), 0, s, M, off, in, out, (int)nc, lo,   \
+                         nl);                                                                                        \
+    return check_hip(hipGetLastError(), "divergence/gradient kernel launch");                                       \
+  }
+  X(3, 2) X(4, 3) X(5, 4) X(6, 5)
+#undef X
+  return set_error(DG_ERR_UNSUPPORTED, "pressure gradient / velocity divergence: degrees not compiled");
 }
 
 }  // namespace dgwm

@@ -149,12 +149,8 @@ int dg_dual_splitting_step(const dg_mesh* m, const dg_step_params* sp, const dou
   // 2 pressure: rhs = -(gamma0/dt) C u^ + wall term of the Neumann data
   DG_TRY(launch_divgrad(m, true, W.uh, W.rhs, s));
   hipLaunchKernelGGL(st_scale, dim3(ew_blocks(npr)), dim3(256), 0, s, W.rhs, npr, -sp->gamma0 / sp->dt);
-  DG_TRY(launch_vorticity_rhs(m, u_n, W.om0, s));
-  DG_TRY(launch_inverse_mass(m, W.om0, W.om0, s));
-  if (J == 2) {
-    DG_TRY(launch_vorticity_rhs(m, u_nm1, W.om1, s));
-    DG_TRY(launch_inverse_mass(m, W.om1, W.om1, s));
-  }
+  DG_TRY(launch_vorticity(m, u_n, W.om0, s));
+  if (J == 2) DG_TRY(launch_vorticity(m, u_nm1, W.om1, s));
   const double* oms[2] = {W.om0, W.om1};
   DG_TRY(launch_pressure_neumann(m, J, us, oms, sp->beta, sp->f, W.rhs, s));
   dg_solve_stats pst{};

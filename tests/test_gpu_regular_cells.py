@@ -13,6 +13,7 @@ import pytest
 import torch
 
 import oracle as O
+from oracle.step import vorticity_rhs
 from paper_1705_08813_amd import Mesh
 from paper_1705_08813_amd.inputs import MeshConfig, Workload, draw_inputs
 
@@ -66,3 +67,21 @@ def test_viscous_operator_with_inverse_mass(cfg):
     _, st = mesh.solve_helmholtz(nut, gamma, u, u.clone(), rtol=0.5, max_iter=1)
     assert st.iterations == 0
     assert abs(st.rel_resid - 1.0 / 3.0) <= 1e-10
+
+
+@pytest.mark.parametrize("cfg", MESHES, ids=IDS)
+def test_gradient_and_divergence(cfg):
+    inp, mesh, u = _setup(cfg)
+    p = torch.tensor(inp["p"], device="cuda")
+    _close(mesh.apply_pressure_gradient(p), O.pressure_gradient(cfg, inp["p"], tau=inp["tau"]))
+    _close(mesh.apply_velocity_divergence(u), O.velocity_divergence(cfg, inp["u"], tau=inp["tau"]))
+
+
+@pytest.mark.parametrize("cfg", MESHES, ids=IDS)
+def test_vorticity(cfg):
+    inp, mesh, u = _setup(cfg)
+    b = mesh.vorticity_rhs(u)
+    _close(b, vorticity_rhs(cfg, inp["u"], inp["tau"]))
+    # the projection: M^{-1} of that vector (enriched cells by the same solver)
+    om, mb = mesh.vorticity(u), mesh.apply_inverse_mass(b)
+    assert float((om - mb).abs().max()) <= 1e-12 * float(mb.abs().max())
