@@ -167,14 +167,62 @@ void fill_poisson_ops(int np, int nq, double* out) {
   for (int i = 0; i < o.n; ++i) f[i] = (float)out[i];
 }
 
+namespace {
+
+using R = long double;  // the operator tables are rounded once
+
+// I = M^{-1} of a symmetric positive definite matrix by Gauss-Jordan elimination
+void invert(int np, const R (&M)[kMaxP][kMaxP], R (&I)[kMaxP][kMaxP]) {
+  R T[kMaxP][kMaxP];
+  for (int i = 0; i < np; ++i)
+    for (int j = 0; j < np; ++j) {
+      T[i][j] = M[i][j];
+      I[i][j] = i == j;
+    }
+  for (int c = 0; c < np; ++c) {
+    const R p = 1 / T[c][c];
+    for (int j = 0; j < np; ++j) {
+      T[c][j] *= p;
+      I[c][j] *= p;
+    }
+    for (int i = 0; i < np; ++i) {
+      if (i == c) continue;
+      const R f = T[i][c];
+      for (int j = 0; j < np; ++j) {
+        T[i][j] -= f * T[c][j];
+        I[i][j] -= f * I[c][j];
+      }
+    }
+  }
+}
+
+}  // namespace
+
+void fill_projection(int np, int nq, double* out) {
+  double gl[kMaxP], g[kMaxQ], w[kMaxQ], v[kMaxQ][kMaxP], d[kMaxP];
+  lobatto_nodes(np, gl);
+  gauss_rule(nq, g, w);
+  R M[kMaxP][kMaxP] = {}, I[kMaxP][kMaxP];
+  for (int q = 0; q < nq; ++q) {
+    lagrange_eval(gl, np, g[q], v[q], d);
+    for (int i = 0; i < np; ++i)
+      for (int j = 0; j < np; ++j) M[i][j] += (R)w[q] * v[q][i] * v[q][j];
+  }
+  invert(np, M, I);
+  for (int i = 0; i < np; ++i)
+    for (int q = 0; q < nq; ++q) {
+      R a = 0;
+      for (int j = 0; j < np; ++j) a += I[i][j] * v[q][j];
+      out[i * nq + q] = (double)(a * w[q]);
+    }
+}
+
 void fill_lin_ops(int np, double* out) {
   const LinOps o = lin_ops(np);
-  // long double throughout: the tables are rounded once
-  using R = long double;
   double gl[kMaxP], g[kMaxQ], w[kMaxQ], v[kMaxP], d[kMaxP];
   lobatto_nodes(np, gl);
   gauss_rule(np, g, w);  // exact for the products of two basis functions
-  R M[kMaxP][kMaxP] = {}, K[kMaxP][kMaxP] = {}, C[kMaxP][kMaxP] = {}, I[kMaxP][kMaxP] = {};
+  R M[kMaxP][kMaxP] = {}, K[kMaxP][kMaxP] = {}, C[kMaxP][kMaxP] = {}, I[kMaxP][kMaxP];
   for (int q = 0; q < np; ++q) {
     lagrange_eval(gl, np, g[q], v, d);
     for (int i = 0; i < np; ++i)
@@ -184,29 +232,7 @@ void fill_lin_ops(int np, double* out) {
         C[i][j] += (R)w[q] * d[i] * v[j];
       }
   }
-  {  // I = M^{-1} by Gauss-Jordan elimination (M is symmetric positive definite)
-    R T[kMaxP][kMaxP];
-    for (int i = 0; i < np; ++i)
-      for (int j = 0; j < np; ++j) {
-        T[i][j] = M[i][j];
-        I[i][j] = i == j;
-      }
-    for (int c = 0; c < np; ++c) {
-      const R p = 1 / T[c][c];
-      for (int j = 0; j < np; ++j) {
-        T[c][j] *= p;
-        I[c][j] *= p;
-      }
-      for (int i = 0; i < np; ++i) {
-        if (i == c) continue;
-        const R f = T[i][c];
-        for (int j = 0; j < np; ++j) {
-          T[i][j] -= f * T[c][j];
-          I[i][j] -= f * I[c][j];
-        }
-      }
-    }
-  }
+  invert(np, M, I);
   double nd0[kMaxP], nd1[kMaxP];
   lagrange_eval(gl, np, 0.0, v, nd0);
   lagrange_eval(gl, np, 1.0, v, nd1);

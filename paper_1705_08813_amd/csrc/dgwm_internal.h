@@ -102,6 +102,11 @@ __host__ __device__ constexpr LinOps lin_ops(int np) {
 // offset of that block from the start of the velocity tables
 __host__ __device__ constexpr int lin_offset(int np, int nq, int nqy) { return tab_layout(np, nq, nqy).size + nq + nqy; }
 
+// Behind that: Pi[i][q] = (M^{-1} S^T W)_{iq}, the 1-D discrete L2 projection
+// of point values (rule q) onto the velocity basis; with it a point field on a
+// face acts on every polynomial test function like the nodal field Pi x Pi.
+__host__ __device__ constexpr int proj_offset(int np, int nq, int nqy) { return lin_offset(np, nq, nqy) + lin_ops(np).size; }
+
 // 1-D operators between the velocity basis N (npu nodes) and the pressure
 // basis P (npp nodes), behind the block above:
 //   Mup[i][a] = int N_i P_a,
@@ -111,7 +116,7 @@ struct MixOps {
   int Mup, Gu, Gp, size;
 };
 __host__ __device__ constexpr MixOps mix_ops(int npu, int npp) { return MixOps{0, npu * npp, 2 * npu * npp, 3 * npu * npp}; }
-__host__ __device__ constexpr int mix_offset(int np, int nq, int nqy) { return lin_offset(np, nq, nqy) + lin_ops(np).size; }
+__host__ __device__ constexpr int mix_offset(int np, int nq, int nqy) { return proj_offset(np, nq, nqy) + np * nq; }
 
 // Points of the enrichment tables of one enriched cell: the volume rule
 // nq x nqy x nq, then the six faces f = 2d + s in order.  Face (d,s) has
@@ -131,6 +136,7 @@ __host__ __device__ constexpr int psi_points(int nq, int nqy) { return psi_face_
 void fill_tables(int np, int nq, int nqy, double* out);
 void fill_poisson_ops(int np, int nq, double* out);  // poi_ops(np).size doubles
 void fill_lin_ops(int np, double* out);              // lin_ops(np).size doubles
+void fill_projection(int np, int nq, double* out);   // np x nq doubles
 void fill_mix_ops(int npu, int npp, double* out);    // mix_ops(npu, npp).size doubles
 void gauss_rule(int n, double* x, double* w);
 void lobatto_nodes(int n, double* x);

@@ -33,6 +33,8 @@ struct MeshDev {
   int nq_wn;          // wall-normal points of enriched cells (the point layout of their tables)
   const double* nut;  // eddy viscosity [enr][psi_pts] of the multiscale viscous operator (else nullptr)
   int ops_off;        // offset of the Poisson operator tables (poi_ops) inside tab
+  int lin_off;        // offset of the velocity's 1-D operators (lin_ops) inside tab
+  int proj_off;       // offset of the projection table
 };
 
 // Enriched index of cell (ex, ey, ez) or -1.
@@ -43,6 +45,70 @@ __device__ __forceinline__ int64_t enr_index(const MeshDev& M, int ex, int ey, i
   else if (ey == M.ny - 1 && M.upper_slot >= 0) slot = M.upper_slot;
   if (slot < 0) return -1;
   return ex + M.nx * (slot + M.nslots * ez);  // below 2^31 like the cell count
+}
+
+// The mesh's 1-D tables in the constant address space: uniform reads become
+// scalar loads, also where the pointer itself comes from memory (batched
+// launches).  The tables are written once, at set-up.  Every call gives a
+// pointer that the compiler takes for a new one, so coefficients are loaded
+// again where they are used instead of being held (and spilled) in between.
+template <typename T>
+using ConstTab = const __attribute__((address_space(4))) T*;
+template <typename T>
+__device__ __forceinline__ ConstTab<T> const_tab(const double* p) {
+  const uintptr_t a = (uintptr_t)p;
+  uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)a), hi = __builtin_amdgcn_readfirstlane((int)(a >> 32));
+  asm volatile("" : "+s"(lo), "+s"(hi));
+  return (ConstTab<T>)((uintptr_t)lo | ((uintptr_t)hi << 32));
+}
+
+// Neighbour of cell e = (ex, ey, ez) across face (D, S), or -1 for a wall.
+__device__ __forceinline__ int cell_nb(const MeshDev& M, int e, int ex, int ey, int ez, int D, int S) {
+  const int j = D == 0 ? ex : (D == 1 ? ey : ez);
+  const int nmax = D == 0 ? M.nx : (D == 1 ? M.ny : M.nz);
+  const int step = D == 0 ? 1 : (D == 1 ? M.nx : M.nx * M.ny);
+  if (S ? j == nmax - 1 : j == 0) {
+    if (D == 1 && !M.fully_periodic) return -1;
+    return S ? e - (nmax - 1) * step : e + (nmax - 1) * step;
+  }
+  return S ? e + step : e - step;
+}
+
+// Line (a, b) of nodes along direction D (a, b: indices of the tangential
+// directions in order): first node and stride in a cell's vector.
+template <int NP>
+__device__ __forceinline__ void vec_line(int D, int a, int b, int& base, int& stride) {
+  base = D == 0 ? NP * (a + NP * b) : (D == 1 ? a + NP * NP * b : a + NP * b);
+  stride = D == 0 ? 1 : (D == 1 ? NP : NP * NP);
+}
+
+// LDS layout of one nodal component: node (i, j, m) at i + SJ j + SK m, SC
+// values; the odd row length spreads the lines that a wavefront touches over
+// the banks.
+template <int NP>
+struct NodeLds {
+  static constexpr int SJ = NP | 1, SK = SJ * NP, SC = SK * NP;
+  static __device__ __forceinline__ void line(int D, int a, int b, int& base, int& stride) {
+    base = D == 0 ? SJ * a + SK * b : (D == 1 ? a + SK * b : a + SJ * b);
+    stride = D == 0 ? 1 : (D == 1 ? SJ : SK);
+  }
+};
+
+// block -> contiguous cell ranges per XCD (workgroups are dealt round-robin
+// over the 8 XCDs), so that neighbouring cells share an L2
+__device__ __forceinline__ int xcd_block(int nb, int bid) {
+  const int q8 = nb >> 3, r8 = nb & 7, xcd = bid & 7, m8 = bid >> 3;
+  return xcd * q8 + (xcd < r8 ? xcd : r8) + m8;
+}
+
+// The value of the neighbouring lane (lane ^ 1), without LDS.
+__device__ __forceinline__ float pair_swap(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double pair_swap(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0xB1, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0xB1, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
 }
 
 // Apply a 1-D matrix along direction DIR (0 = x fastest) to `ncomp` stacked

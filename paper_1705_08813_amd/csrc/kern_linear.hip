@@ -18,38 +18,9 @@ struct SepShape {
   static constexpr int NP2 = NP * NP, NP3 = NP2 * NP;
   static constexpr int TPC = 3 * NP2;                        // threads of a cell
   static constexpr int CB = 256 / TPC;                       // cells of a workgroup
-  // LDS layout of one component: node (i, j, m) at i + SJ j + SK m; the odd
-  // row length spreads the lines that a wavefront touches over the banks
-  static constexpr int SJ = NP | 1, SK = SJ * NP, SC = SK * NP;
+  static constexpr int SJ = NodeLds<NP>::SJ, SK = NodeLds<NP>::SK, SC = NodeLds<NP>::SC;
   static constexpr int JP = 12 * NP2;                        // tangential jumps [D][2][side][NP2]
 };
-
-// Line (a, b) of nodes along direction D: first node and stride, in a vector
-// of the cell (GLOBAL) or in LDS.
-template <int NP>
-__device__ __forceinline__ void vec_line(int D, int a, int b, int& base, int& stride) {
-  constexpr int NP2 = NP * NP;
-  base = D == 0 ? NP * (a + NP * b) : (D == 1 ? a + NP2 * b : a + NP * b);
-  stride = D == 0 ? 1 : (D == 1 ? NP : NP2);
-}
-template <int NP>
-__device__ __forceinline__ void lds_line(int D, int a, int b, int& base, int& stride) {
-  using Sh = SepShape<NP>;
-  base = D == 0 ? Sh::SJ * a + Sh::SK * b : (D == 1 ? a + Sh::SK * b : a + Sh::SJ * b);
-  stride = D == 0 ? 1 : (D == 1 ? Sh::SJ : Sh::SK);
-}
-
-// Neighbour of cell e across face (D, S), or -1 for a wall.
-__device__ __forceinline__ int sep_nb(const MeshDev& M, int e, int ex, int ey, int ez, int D, int S) {
-  const int j = D == 0 ? ex : (D == 1 ? ey : ez);
-  const int nmax = D == 0 ? M.nx : (D == 1 ? M.ny : M.nz);
-  const int step = D == 0 ? 1 : (D == 1 ? M.nx : M.nx * M.ny);
-  if (S ? j == nmax - 1 : j == 0) {
-    if (D == 1 && !M.fully_periodic) return -1;
-    return S ? e - (nmax - 1) * step : e + (nmax - 1) * step;
-  }
-  return S ? e + step : e - step;
-}
 
 // What a cell's line along D meets at its two ends: the neighbours' values
 // and normal derivatives, the penalties, and walls.
@@ -110,7 +81,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
   Ends<T> en[3];
   T x[NP], qz[NP];
   // the scalar operator on a line, its jumps and (D = c) its weak derivative
-  auto line = [&](int D, const T (&p)[NP], const Ends<T>& n, T (&q)[NP]) {
+  auto line = [&](int D, const T (&p)[NP], const Ends<T>& n, T (&q)[NP]) __attribute__((always_inline)) {
     const T rd = ih[D], kap = c == D ? T(2) : T(1);
     T d0 = 0, d1 = 0;
 #pragma unroll
@@ -136,7 +107,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
       const T a0 = T(0.5) * (p[0] + (n.wall[0] ? p[0] : n.v[0]));
       const T a1 = T(0.5) * (p[NP - 1] + (n.wall[1] ? p[NP - 1] : n.v[1]));
       int wb, ws;
-      lds_line<NP>(D, a, b, wb, ws);
+      NodeLds<NP>::line(D, a, b, wb, ws);
       T* o = sw + c * Sh::SC + wb;
 #pragma unroll
       for (int l = 0; l < NP; ++l) {
@@ -169,7 +140,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
       vec_line<NP>(D, a, b, vb, vs);
 #pragma unroll
       for (int S = 0; S < 2; ++S) {
-        const int nb = sep_nb(M, e, ex, ey, ez, D, S);
+        const int nb = cell_nb(M, e, ex, ey, ez, D, S);
         T rn = ih[D], v = 0, d = 0;
         if (nb >= 0) {
           const T* pn = u + ((int64_t)nb * 3 + c) * NP3 + vb;
@@ -205,7 +176,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
   if (live) {
     int lb, ls;
     T q[NP];
-    lds_line<NP>(1, a, b, lb, ls);
+    NodeLds<NP>::line(1, a, b, lb, ls);
     T* p = su + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
@@ -213,7 +184,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
     p = sr + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) p[l * ls] += q[l];
-    lds_line<NP>(2, a, b, lb, ls);
+    NodeLds<NP>::line(2, a, b, lb, ls);
     p = su + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
@@ -225,7 +196,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
   if (live) {
     const int d1 = c == 0 ? 1 : 0, d2 = c == 2 ? 1 : 2;  // the tangential directions, d1 along a, d2 along b
     int lb, ls;
-    lds_line<NP>(c, a, b, lb, ls);
+    NodeLds<NP>::line(c, a, b, lb, ls);
     const T* w1 = sw + d1 * Sh::SC + lb;
     const T* w2 = sw + d2 * Sh::SC + lb;
 #pragma unroll
@@ -259,7 +230,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
   const T nu = T(M.nu);
   if (live) {  // along z: add the z part; mass matrix
     int lb, ls;
-    lds_line<NP>(2, a, b, lb, ls);
+    NodeLds<NP>::line(2, a, b, lb, ls);
     T* p = sr + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls] + qz[l];
@@ -278,7 +249,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
   if (!MINV) {
     if (live) {
       int lb, ls;
-      lds_line<NP>(1, a, b, lb, ls);
+      NodeLds<NP>::line(1, a, b, lb, ls);
       T* p = sr + c * Sh::SC + lb;
 #pragma unroll
       for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
@@ -309,13 +280,6 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
       o[l] = sc * acc;
     }
   }
-}
-
-// block -> contiguous cell ranges per XCD (workgroups are dealt round-robin
-// over the 8 XCDs), so that neighbouring cells share an L2
-__device__ __forceinline__ int xcd_block(int nb, int bid) {
-  const int q8 = nb >> 3, r8 = nb & 7, xcd = bid & 7, m8 = bid >> 3;
-  return xcd * q8 + (xcd < r8 ? xcd : r8) + m8;
 }
 
 template <int NP, bool MINV>
@@ -381,8 +345,8 @@ __global__ __launch_bounds__(256) void vorticity_regular_kernel(const MeshDev M,
   __syncthreads();
   const double f1 = sg * (d1 == 0 ? ih[0] : ih[1]), f2 = -sg * (d2 == 1 ? ih[1] : ih[2]);
   int lb1, ls1, lb2, ls2;
-  lds_line<NP>(d1, a, b, lb1, ls1);
-  lds_line<NP>(d2, a, b, lb2, ls2);
+  NodeLds<NP>::line(d1, a, b, lb1, ls1);
+  NodeLds<NP>::line(d2, a, b, lb2, ls2);
   if (live) {
     load(su + d2 * Sh::SC + lb1, ls1);
 #pragma unroll
@@ -403,7 +367,7 @@ __global__ __launch_bounds__(256) void vorticity_regular_kernel(const MeshDev M,
   if (!MINV) {
     // the other tangential direction: y for rows x and y, z for row z
     int lb, ls;
-    lds_line<NP>(r == 2 ? 2 : 1, a, b, lb, ls);
+    NodeLds<NP>::line(r == 2 ? 2 : 1, a, b, lb, ls);
     if (live) {
       load(sr + lb, ls);
 #pragma unroll
@@ -459,7 +423,7 @@ __global__ __launch_bounds__(256) void gradient_regular_kernel(const MeshDev M, 
     const int ex = i % M.nx, t0 = i / M.nx;
     const int ey = layer_lo + t0 % nlayers, ez = t0 / nlayers;
     const int e = ex + M.nx * (ey + M.ny * ez);
-    s_e[tid] = f < 0 ? e : sep_nb(M, e, ex, ey, ez, f >> 1, f & 1);
+    s_e[tid] = f < 0 ? e : cell_nb(M, e, ex, ey, ez, f >> 1, f & 1);
   }
   __syncthreads();
   for (int it = tid; it < nc * NPV; it += 256) {
@@ -616,7 +580,7 @@ __global__ __launch_bounds__(256) void divergence_regular_kernel(const MeshDev M
     const int ex = i % M.nx, t0 = i / M.nx;
     const int ey = layer_lo + t0 % nlayers, ez = t0 / nlayers;
     const int e = ex + M.nx * (ey + M.ny * ez);
-    s_e[tid] = f < 0 ? e : sep_nb(M, e, ex, ey, ez, f >> 1, f & 1);
+    s_e[tid] = f < 0 ? e : cell_nb(M, e, ex, ey, ez, f >> 1, f & 1);
   }
   __syncthreads();
   for (int it = tid; it < nc * NV; it += 256) {

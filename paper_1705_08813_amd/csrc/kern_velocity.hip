@@ -17,6 +17,7 @@
 #include <cstring>
 
 #include "batch.h"
+#include "velocity.h"
 
 namespace dgwm {
 
@@ -1903,22 +1904,22 @@ __host__ __device__ constexpr int vel_wg_per_cu() {
 // (degree-1 enrichment weights, LE = 8, always take the general path)
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, int LE = 1>
 __device__ __forceinline__ void vel_cell(const MeshDev& M, const T* __restrict__ u, T* __restrict__ r, int b,
-                                         int layer_lo, int nlayers) {
+                                         int layer_lo, int nlayers, int layer_step = 1) {
   if constexpr (!CURVED && LE == 1 && vel_use_affine<T>() && AffShape<T, NP, NQ, NQY>::fits)
     vel_cell_affine<T, NP, NQ, NQY, ENR>(M, u, r, b, layer_lo, nlayers);
   else
-    vel_cell_general<T, NP, NQ, NQY, ENR, CURVED, false, LE>(M, u, r, b, layer_lo, nlayers);
+    vel_cell_general<T, NP, NQ, NQY, ENR, CURVED, false, LE>(M, u, r, b, layer_lo, nlayers, layer_step);
 }
 
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, int LE = 1>
 __global__ __launch_bounds__(256, (vel_wg_per_cu<T, NP, NQ, NQY, ENR, CURVED, LE>())) void vel_kernel(const MeshDev M, const T* __restrict__ u, T* __restrict__ r,
-                                                  int layer_lo, int nlayers) {
+                                                  int layer_lo, int nlayers, int layer_step) {
   // contiguous cell ranges per XCD (workgroups are dealt round-robin over
   // the 8 XCDs), so neighbouring cells share an L2
   const int nb = gridDim.x, bid = blockIdx.x;
   const int q8 = nb >> 3, r8 = nb & 7, xcd = bid & 7, m8 = bid >> 3;
   const int blk = xcd * q8 + (xcd < r8 ? xcd : r8) + m8;
-  vel_cell<T, NP, NQ, NQY, ENR, CURVED, LE>(M, u, r, blk, layer_lo, nlayers);
+  vel_cell<T, NP, NQ, NQY, ENR, CURVED, LE>(M, u, r, blk, layer_lo, nlayers, layer_step);
 }
 
 }  // namespace
@@ -1935,14 +1936,6 @@ __global__ __launch_bounds__(256, (LE == 8 && ENR) ? 2 : 3) void visc_ms_kernel(
   vel_cell_general<double, NP, NQ, NQY, ENR, false, true, LE>(M, u, r, blk, layer_lo, nlayers, layer_step);
 }
 
-// One mesh of a batched launch.
-struct VelBatchItem {
-  MeshDev M;
-  const void* u;
-  void* r;
-  int layer_lo, nlayers;
-};
-
 namespace {
 
 // Cells of many meshes (same degree and rules) in one launch: block b takes
@@ -1952,59 +1945,50 @@ namespace {
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED>
 __global__ __launch_bounds__(256, (vel_wg_per_cu<T, NP, NQ, NQY, ENR, CURVED>())) void vel_kernel_batched(const VelBatchItem* __restrict__ items,
                                                           const int64_t* __restrict__ prefix, int nitems) {
-  const int64_t b = blockIdx.x;
-  int lo = 0, hi = nitems;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (prefix[mid] <= b) lo = mid; else hi = mid;
-  }
-  lo = __builtin_amdgcn_readfirstlane(lo);
+  const int lo = batch_item(prefix, nitems);
   const VelBatchItem& it = items[lo];
   vel_cell<T, NP, NQ, NQY, ENR, CURVED>(it.M, static_cast<const T*>(it.u), static_cast<T*>(it.r),
-                                        (int)(b - prefix[lo]), it.layer_lo, it.nlayers);
+                                        (int)(blockIdx.x - prefix[lo]), it.layer_lo, it.nlayers);
 }
 
+// Enriched cells, and on curved meshes the others.
 template <typename T, int NP, int NQ, int NQW>
-int launch_vel_t(const dg_mesh* m, const MeshDev& M, const void* u, void* r, hipStream_t s) {
+int launch_vel_t(const dg_mesh* m, const MeshDev& M, const void* u, void* r, bool convective_only, hipStream_t s) {
   const T* uu = static_cast<const T*>(u);
   T* rr = static_cast<T*>(r);
-  const int lo = (m->P.fully_periodic || m->lower_slot < 0) ? 0 : 1;
-  const int hi = (m->P.fully_periodic || m->upper_slot < 0) ? m->P.ny - 1 : m->P.ny - 2;
-  const int nl = hi - lo + 1;
-  if (nl > 0) {
-    const unsigned nb = (unsigned)((int64_t)m->P.nx * nl * m->P.nz);
-    if (m->curved)
-      hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQ, false, true>), dim3(nb), dim3(256), 0, s, M, uu, rr, lo, nl);
-    else
-      hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQ, false, false>), dim3(nb), dim3(256), 0, s, M, uu, rr, lo, nl);
+  const RegularLayers L = regular_layers(m);
+  if (!m->curved) {
+    if (int rc = launch_residual_regular<T>(m, uu, rr, L.lo, L.nl, !convective_only, s)) return rc;
+  } else if (L.nl > 0) {
+    hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQ, false, true>), dim3((unsigned)((int64_t)m->P.nx * L.nl * m->P.nz)),
+                       dim3(256), 0, s, M, uu, rr, L.lo, L.nl, 1);
   }
   if (m->nenr > 0) {
     if (m->curved)
       hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQW, true, true>), dim3((unsigned)m->nenr), dim3(256), 0, s, M, uu,
-                         rr, 0, 0);
+                         rr, 0, 0, 1);
     else
       hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQW, true, false>), dim3((unsigned)m->nenr), dim3(256), 0, s, M,
-                         uu, rr, 0, 0);
+                         uu, rr, 0, 0, 1);
   }
   return check_hip(hipGetLastError(), "velocity kernel launch");
 }
 
-// Degree-1 enrichment weights (flat meshes): the regular cells' kernel reads
-// the neighbours' 24 coefficients across the interface faces.
+// Degree-1 enrichment weights (flat meshes): the cells next to an enriched
+// layer take the general kernel, which reads the neighbours' 24 coefficients.
 template <typename T, int NP, int NQ, int NQW>
-int launch_vel_l1_t(const dg_mesh* m, const MeshDev& M, const void* u, void* r, hipStream_t s) {
+int launch_vel_l1_t(const dg_mesh* m, const MeshDev& M, const void* u, void* r, bool convective_only, hipStream_t s) {
   const T* uu = static_cast<const T*>(u);
   T* rr = static_cast<T*>(r);
-  const int lo = (m->P.fully_periodic || m->lower_slot < 0) ? 0 : 1;
-  const int hi = (m->P.fully_periodic || m->upper_slot < 0) ? m->P.ny - 1 : m->P.ny - 2;
-  const int nl = hi - lo + 1;
-  if (nl > 0) {
-    const unsigned nb = (unsigned)((int64_t)m->P.nx * nl * m->P.nz);
-    hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQ, false, false, 8>), dim3(nb), dim3(256), 0, s, M, uu, rr, lo, nl);
-  }
+  const RegularLayers L = regular_layers(m);
+  if (int rc = launch_residual_regular<T>(m, uu, rr, L.ilo, L.inl, !convective_only, s)) return rc;
+  if (L.xnl > 0)
+    hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQ, false, false, 8>),
+                       dim3((unsigned)((int64_t)m->P.nx * L.xnl * m->P.nz)), dim3(256), 0, s, M, uu, rr, L.xlo, L.xnl,
+                       L.xstep);
   if (m->nenr > 0)
     hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQW, true, false, 8>), dim3((unsigned)m->nenr), dim3(256), 0, s, M, uu,
-                       rr, 0, 0);
+                       rr, 0, 0, 1);
   return check_hip(hipGetLastError(), "velocity kernel launch");
 }
 
@@ -2039,6 +2023,8 @@ MeshDev velocity_meshdev(const dg_mesh* m) {
   M.tauF = m->tauF;
   M.nq_wn = m->P.nq_wn;
   M.nut = nullptr;
+  M.lin_off = lin_offset(m->np_u, m->P.nq_u, m->P.nq_wn);
+  M.proj_off = proj_offset(m->np_u, m->P.nq_u, m->P.nq_wn);
   return M;
 }
 
@@ -2060,15 +2046,19 @@ MeshDev velocity_meshdev(const dg_mesh* m) {
   X(5, 7, 8)
 
 template <typename T, int NP, int NQ, int NQW, bool CURVED>
-static void launch_batch_group(const VelBatchItem* d_items_reg, const int64_t* d_pre_reg, int nreg, int64_t tot_reg,
+static int launch_batch_group(const VelBatchItem* d_items_reg, const int64_t* d_pre_reg, int nreg, int64_t tot_reg,
                                const VelBatchItem* d_items_enr, const int64_t* d_pre_enr, int nenr, int64_t tot_enr,
                                hipStream_t s) {
-  if (nreg > 0 && tot_reg > 0)
+  if constexpr (!CURVED) {
+    if (int rc = launch_residual_regular_batched<T>(NP, NQ, d_items_reg, d_pre_reg, nreg, tot_reg, s)) return rc;
+  } else if (nreg > 0 && tot_reg > 0) {
     hipLaunchKernelGGL((vel_kernel_batched<T, NP, NQ, NQ, false, CURVED>), dim3((unsigned)tot_reg), dim3(256), 0, s,
                        d_items_reg, d_pre_reg, nreg);
+  }
   if (nenr > 0 && tot_enr > 0)
     hipLaunchKernelGGL((vel_kernel_batched<T, NP, NQ, NQW, true, CURVED>), dim3((unsigned)tot_enr), dim3(256), 0, s,
                        d_items_enr, d_pre_enr, nenr);
+  return DG_OK;
 }
 
 bool velocity_supported(int np, int nq, int nqy) {
@@ -2144,8 +2134,8 @@ int launch_velocity(const dg_mesh* m, dg_prec prec, const void* u, void* r, hipS
   if (m->nle != 1 && m->nenr > 0) {
 #define X(a, b, c)                                                                 \
   if (np == a && nq == b && nqw == c) {                                            \
-    return prec == DG_F64 ? launch_vel_l1_t<double, a, b, c>(m, M, u, r, s)        \
-                          : launch_vel_l1_t<float, a, b, c>(m, M, u, r, s);        \
+    return prec == DG_F64 ? launch_vel_l1_t<double, a, b, c>(m, M, u, r, convective_only, s)        \
+                          : launch_vel_l1_t<float, a, b, c>(m, M, u, r, convective_only, s);        \
   }
     DG_VEL_L1_COMBOS(X)
 #undef X
@@ -2155,8 +2145,8 @@ int launch_velocity(const dg_mesh* m, dg_prec prec, const void* u, void* r, hipS
   // without enriched cells only the regular kernel runs: nq_wn is irrelevant
 #define X(a, b, c)                                                                 \
   if (np == a && nq == b && (nqw == c || m->nenr == 0)) {                          \
-    return prec == DG_F64 ? launch_vel_t<double, a, b, c>(m, M, u, r, s)           \
-                          : launch_vel_t<float, a, b, c>(m, M, u, r, s);           \
+    return prec == DG_F64 ? launch_vel_t<double, a, b, c>(m, M, u, r, convective_only, s)           \
+                          : launch_vel_t<float, a, b, c>(m, M, u, r, convective_only, s);           \
   }
   DG_VEL_COMBOS(X)
 #undef X
@@ -2257,7 +2247,9 @@ int launch_velocity_batched(const dg_mesh* const* meshes, int n, dg_prec prec, c
         const dg_mesh* m = meshes[i];
         const RegularLayers RL = regular_layers(m);
         const int lo = RL.lo, nl = RL.nl;
-        const int64_t nb = cls == 0 ? (nl > 0 ? (int64_t)m->P.nx * nl * m->P.nz : 0) : m->nenr;
+        const int64_t cells = cls == 0 ? (nl > 0 ? (int64_t)m->P.nx * nl * m->P.nz : 0) : m->nenr;
+        const int cb = cls == 0 && !m->curved ? residual_cells_per_block(m->np_u) : 1;
+        const int64_t nb = (cells + cb - 1) / cb;
         if (nb == 0) continue;
         VelBatchItem it{};
         it.M = velocity_meshdev(m);
@@ -2265,6 +2257,7 @@ int launch_velocity_batched(const dg_mesh* const* meshes, int n, dg_prec prec, c
         it.r = r[i];
         it.layer_lo = lo;
         it.nlayers = nl;
+        it.ncells = (int)cells;
         items.push_back(it);
         pre.push_back(tot);
         tot += nb;
@@ -2297,23 +2290,24 @@ int launch_velocity_batched(const dg_mesh* const* meshes, int n, dg_prec prec, c
     done = true;                                                                                                 \
     if (prec == DG_F64) {                                                                                        \
       if (G.k.curved)                                                                                            \
-        launch_batch_group<double, a, b, c, true>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,              \
+        rc = launch_batch_group<double, a, b, c, true>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,              \
                                                   d_items + G.ienr, d_pre + G.penr, G.nenr, G.tenr, s);          \
       else                                                                                                       \
-        launch_batch_group<double, a, b, c, false>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,             \
+        rc = launch_batch_group<double, a, b, c, false>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,             \
                                                    d_items + G.ienr, d_pre + G.penr, G.nenr, G.tenr, s);         \
     } else {                                                                                                     \
       if (G.k.curved)                                                                                            \
-        launch_batch_group<float, a, b, c, true>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,               \
+        rc = launch_batch_group<float, a, b, c, true>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,               \
                                                  d_items + G.ienr, d_pre + G.penr, G.nenr, G.tenr, s);           \
       else                                                                                                       \
-        launch_batch_group<float, a, b, c, false>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,              \
+        rc = launch_batch_group<float, a, b, c, false>(d_items + G.ireg, d_pre + G.preg, G.nreg, G.treg,              \
                                                   d_items + G.ienr, d_pre + G.penr, G.nenr, G.tenr, s);          \
     }                                                                                                            \
   }
     DG_VEL_COMBOS(X)
 #undef X
     if (!done) return set_error(DG_ERR_UNSUPPORTED, "velocity combination not compiled");
+    if (rc) return rc;
   }
   return check_hip(hipGetLastError(), "batched velocity launch");
 }

@@ -85,3 +85,12 @@ def test_vorticity(cfg):
     # the projection: M^{-1} of that vector (enriched cells by the same solver)
     om, mb = mesh.vorticity(u), mesh.apply_inverse_mass(b)
     assert float((om - mb).abs().max()) <= 1e-12 * float(mb.abs().max())
+
+
+@pytest.mark.parametrize("cfg", MESHES, ids=IDS)
+def test_residual(cfg):
+    """Convective terms by the line-fused quadrature, viscous ones from 1-D
+    operators, and the enriched neighbour's psi u~ on the interface faces."""
+    inp, mesh, u = _setup(cfg)
+    _close(mesh.apply_velocity_residual(u), O.velocity_residual(cfg, inp["u"], inp["tau"]))
+    _close(mesh.apply_convective(u), O.convective_residual(cfg, inp["u"], inp["tau"]))
