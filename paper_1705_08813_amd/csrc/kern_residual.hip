@@ -69,22 +69,23 @@ __device__ __forceinline__ void residual_cells(const MeshDev& M, const T* __rest
   constexpr int HQ = (NQ + 1) / 2, HP = (NP + 1) / 2;
   constexpr LinOps O = lin_ops(NP);
   constexpr auto& tb = ct::tab<NP, NQ>;
-  constexpr bool MEM = sizeof(T) == 8;  // FP64 coefficients come as scalar loads, FP32 ones as literals
+  constexpr bool F64 = sizeof(T) == 8;
   __shared__ T s_mem[CB * Sh::CELL];
   __shared__ CellInfo<T> s_ci[CB];
   __shared__ T s_psi[CB * 2 * NP2];  // enriched y neighbours: psi projected on the face basis
   __shared__ T s_ut[CB * 6];         // their coefficients
   __shared__ T s_e[NP2], s_w[NQ];
   const int tid = threadIdx.x;
-  const double* const ops_at = M.tab + M.lin_off + (MEM ? 0 : O.f32);
-  ConstTab<T> ops = const_tab<T>(ops_at);
-  ConstTab<double> tabS = const_tab<double>(M.tab);
+  // coefficients come as wide scalar loads from the mesh's tables
+  const double* const ops_at = M.tab + M.lin_off + (F64 ? 0 : O.f32);
+  const double* const S_at = M.tab + (F64 ? 0 : M.proj_off + NP * NQ);
+  ConstTab<T> ops = const_tab<T>(ops_at), tabS = const_tab<T>(S_at);
   auto phase = [&]() __attribute__((always_inline)) {  // (see const_tab)
     __syncthreads();
     ops = const_tab<T>(ops_at);
-    tabS = const_tab<double>(M.tab);
+    tabS = const_tab<T>(S_at);
   };
-  auto S = [&](int q, int i) { return MEM ? T(tabS[q * NP + i]) : T(tb.S[q][i]); };
+  auto S = [&](int q, int i) { return tabS[q * NP + i]; };
   const int nc = CB == 1 ? 1 : (ncells - first < CB ? ncells - first : CB);
 
   if (tid < nc) {
