@@ -285,7 +285,8 @@ int launch_eddy_viscosity(const dg_mesh* m, const double* u, double c_des, doubl
 // inverse_mass: out = M^{-1} A u, one pass where the operator allows it
 int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double* u, double* out, hipStream_t s,
                               bool inverse_mass = false);
-// the same operator on the layers [lo, lo + nl) without enriched neighbours, from 1-D operators (kern_linear.hip)
+// the same operator on the layers [lo, lo + nl) of cells without enrichment (enriched neighbours: l = 0 only), from
+// 1-D operators (kern_linear.hip)
 int launch_viscous_regular(const dg_mesh* m, const double* u, double* out, int lo, int nl, bool inverse_mass,
                            hipStream_t s);
 // div-div penalty: tau_D per cell from u (tau = true, out: ncell doubles) or out = D u with tau_d

@@ -82,6 +82,25 @@ __device__ __forceinline__ void vec_line(int D, int a, int b, int& base, int& st
   stride = D == 0 ? 1 : (D == 1 ? NP : NP * NP);
 }
 
+// psi of enriched cell en on its face f (2 D + side), projected onto the face
+// basis (Pi x Pi), at face node (a, b): what a polynomial test sees of it.  For
+// y faces, whose rule is n_q x n_q on both sides.
+template <int NP, int NQ>
+__device__ __forceinline__ double psi_face_node(const MeshDev& M, int en, int f, int a, int b) {
+  const double* ps = M.psi + ((size_t)en * M.psi_pts + M.psi_off[1 + f]) * 4;
+  const double* p1 = M.tab + M.proj_off + a * NQ;
+  const double* p2 = M.tab + M.proj_off + b * NQ;
+  double acc = 0;
+#pragma unroll 1
+  for (int q2 = 0; q2 < NQ; ++q2) {
+    double t = 0;
+#pragma unroll
+    for (int q1 = 0; q1 < NQ; ++q1) t += p1[q1] * ps[(q1 + NQ * q2) * 4];
+    acc += p2[q2] * t;
+  }
+  return acc;
+}
+
 // LDS layout of one nodal component: node (i, j, m) at i + SJ j + SK m, SC
 // values; the odd row length spreads the lines that a wavefront touches over
 // the banks.

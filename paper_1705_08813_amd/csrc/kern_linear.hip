@@ -23,15 +23,18 @@ struct SepShape {
 };
 
 // What a cell's line along D meets at its two ends: the neighbours' values
-// and normal derivatives, the penalties, and walls.
+// and normal derivatives, what an enriched neighbour's psi u~ adds to its
+// value in the jump, the penalties, and walls.
 template <typename T>
 struct Ends {
-  T v[2], d[2], tau[2];
+  T v[2], d[2], tau[2], ps[2];
   bool wall[2];
 };
 
 // Viscous interior-penalty operator (adjoint sign theta) of a cell and its six
-// polynomial neighbours in nodal form,
+// neighbours in nodal form (an enriched neighbour's psi u~ enters the jumps
+// only, as on the interface faces of eq. viscous_multiscale, projected onto
+// the face basis),
 //   V u = nu |J| (M x M x M) R,   R_c = sum_D Q_D u_c + ih_c Dn_c (sum_{d != c} W_d) + sum_s l_s Y_{c,s},
 // with the mass matrix M taken out of every term so that one array per
 // component collects them all:
@@ -52,7 +55,7 @@ struct Ends {
 // the quadrature kernel took 1145 us and the inverse mass another 72 us; about
 // 70 FMAs per unknown, so what bounds it are the seven reads of u (own cell and
 // six neighbours, mostly from L2) and the barriers between the six phases.
-template <typename T, int NP, bool MINV>
+template <typename T, int NP, int NQ, bool MINV>
 __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T theta, const T* __restrict__ u,
                                               T* __restrict__ r, int first, int ncells, int layer_lo, int nlayers) {
   using Sh = SepShape<NP>;
@@ -63,8 +66,12 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
   __shared__ T s_r[CB * 3 * Sh::SC];
   __shared__ T s_j[CB * Sh::JP];
   __shared__ T s_e[NP2];
-  const T* ops = sizeof(T) == 8 ? reinterpret_cast<const T*>(M.tab + lin_off)
-                                : reinterpret_cast<const T*>(M.tab + lin_off + O.f32);
+  const double* const ops_at = M.tab + lin_off + (sizeof(T) == 8 ? 0 : O.f32);
+  ConstTab<T> ops = const_tab<T>(ops_at);
+  auto phase = [&]() __attribute__((always_inline)) {  // (see const_tab)
+    __syncthreads();
+    ops = const_tab<T>(ops_at);
+  };
   const int tid = threadIdx.x;
   const int cell = tid / Sh::TPC, t = tid - cell * Sh::TPC;
   const int c = t / NP2, k = t - c * NP2;
@@ -92,7 +99,8 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
     d0 *= rd;
     d1 *= rd;
     // mirror states on a wall: u+ = -u-, grad u+ = grad u-
-    const T J0 = p[0] - (n.wall[0] ? -p[0] : n.v[0]), J1 = p[NP - 1] - (n.wall[1] ? -p[NP - 1] : n.v[1]);
+    const T J0 = p[0] - (n.wall[0] ? -p[0] : n.v[0] + n.ps[0]);
+    const T J1 = p[NP - 1] - (n.wall[1] ? -p[NP - 1] : n.v[1] + n.ps[1]);
     const T s0 = d0 + (n.wall[0] ? d0 : n.d[0]), s1 = d1 + (n.wall[1] ? d1 : n.d[1]);
     const T G0 = rd * (T(0.5) * kap * s0 + n.tau[0] * J0), G1 = rd * (n.tau[1] * J1 - T(0.5) * kap * s1);
     const T r2 = kap * rd * rd, H0 = T(0.5) * theta * r2 * J0, H1 = -T(0.5) * theta * r2 * J1;
@@ -155,6 +163,13 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
           if (D == 1) rn = T(M.ihy[S ? (ey + 1 == M.ny ? 0 : ey + 1) : (ey == 0 ? M.ny - 1 : ey - 1)]);
           d *= rn;
         }
+        T ps = 0;
+        if (D == 1 && nb >= 0) {
+          const int k1 = (int)enr_index(M, ex, S ? (ey + 1 == M.ny ? 0 : ey + 1) : (ey == 0 ? M.ny - 1 : ey - 1), ez);
+          if (k1 >= 0)
+            ps = T(psi_face_node<NP, NQ>(M, k1, 2 + (1 - S), a, b)) * u[M.enr_off + (int64_t)k1 * 3 + c];
+        }
+        en[D].ps[S] = ps;
         en[D].wall[S] = nb < 0;
         en[D].v[S] = v;
         en[D].d[S] = d;
@@ -171,7 +186,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
       ro[l] = q[l];
     }
   }
-  __syncthreads();
+  phase();
 
   if (live) {
     int lb, ls;
@@ -190,7 +205,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
     line(2, x, en[2], qz);
   }
-  __syncthreads();
+  phase();
 
   // cross terms, on the lines of component c along direction c
   if (live) {
@@ -225,7 +240,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
       p[l * ls] += ihc * acc + ops[O.l0 + l] * y[0] + ops[O.l1 + l] * y[1];
     }
   }
-  __syncthreads();
+  phase();
 
   const T nu = T(M.nu);
   if (live) {  // along z: add the z part; mass matrix
@@ -245,7 +260,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
       p[l * ls] = acc;
     }
   }
-  __syncthreads();
+  phase();
   if (!MINV) {
     if (live) {
       int lb, ls;
@@ -261,7 +276,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
         p[l * ls] = acc;
       }
     }
-    __syncthreads();
+    phase();
   }
   if (live) {
     const T* p = sr + c * Sh::SC + Sh::SJ * k;
@@ -282,11 +297,11 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
   }
 }
 
-template <int NP, bool MINV>
+template <int NP, int NQ, bool MINV>
 __global__ __launch_bounds__(256) void viscous_regular_kernel(const MeshDev M, int lin_off,
                                                               const double* __restrict__ u, double* __restrict__ r,
                                                               int ncells, int layer_lo, int nlayers) {
-  viscous_cells<double, NP, MINV>(M, lin_off, -1.0, u, r, xcd_block(gridDim.x, blockIdx.x) * SepShape<NP>::CB, ncells,
+  viscous_cells<double, NP, NQ, MINV>(M, lin_off, -1.0, u, r, xcd_block(gridDim.x, blockIdx.x) * SepShape<NP>::CB, ncells,
                                   layer_lo, nlayers);
 }
 
@@ -733,18 +748,18 @@ int launch_viscous_regular(const dg_mesh* m, const double* u, double* out, int l
   const MeshDev M = velocity_meshdev(m);
   const int off = lin_offset(m->np_u, m->P.nq_u, m->P.nq_wn);
   const int64_t nc = (int64_t)m->P.nx * nl * m->P.nz;
-#define X(p)                                                                                                       \
-  if (m->np_u == p) {                                                                                              \
-    const unsigned nb = (unsigned)((nc + SepShape<p>::CB - 1) / SepShape<p>::CB);                                  \
-    if (inverse_mass)                                                                                              \
-      hipLaunchKernelGGL((viscous_regular_kernel<p, true>), dim3(nb), dim3(256), 0, s, M, off, u, out, (int)nc, lo, \
-                         nl);                                                                                      \
-    else                                                                                                           \
-      hipLaunchKernelGGL((viscous_regular_kernel<p, false>), dim3(nb), dim3(256), 0, s, M, off, u, out, (int)nc,   \
-                         lo, nl);                                                                                  \
-    return check_hip(hipGetLastError(), "viscous kernel launch");                                                  \
+#define X(p, q)                                                                                                     \
+  if (m->np_u == p && m->P.nq_u == q) {                                                                             \
+    const unsigned nb = (unsigned)((nc + SepShape<p>::CB - 1) / SepShape<p>::CB);                                   \
+    if (inverse_mass)                                                                                               \
+      hipLaunchKernelGGL((viscous_regular_kernel<p, q, true>), dim3(nb), dim3(256), 0, s, M, off, u, out, (int)nc,  \
+                         lo, nl);                                                                                   \
+    else                                                                                                            \
+      hipLaunchKernelGGL((viscous_regular_kernel<p, q, false>), dim3(nb), dim3(256), 0, s, M, off, u, out, (int)nc, \
+                         lo, nl);                                                                                   \
+    return check_hip(hipGetLastError(), "viscous kernel launch");                                                   \
   }
-  X(3) X(4) X(5) X(6)
+  X(3, 4) X(4, 4) X(4, 5) X(5, 7) X(6, 8)
 #undef X
   return set_error(DG_ERR_UNSUPPORTED, "viscous operator: degree not compiled");
 }

@@ -172,20 +172,7 @@ __device__ __forceinline__ void residual_cells(const MeshDev& M, const T* __rest
     const int cell = tid / (2 * NP2), i = tid - cell * 2 * NP2;
     const int s = i / NP2, k = i - s * NP2;
     const int en = cell < nc ? s_ci[cell].enr[s] : -1;
-    if (en >= 0) {
-      const double* ps = M.psi + ((size_t)en * M.psi_pts + M.psi_off[1 + 2 + (1 - s)]) * 4;
-      const double* pi = M.tab + M.proj_off;
-      const double* p1 = pi + (k % NP) * NQ;
-      const double* p2 = pi + (k / NP) * NQ;
-      T acc = 0;
-      for (int q2 = 0; q2 < NQ; ++q2) {
-        T a = 0;
-#pragma unroll
-        for (int q1 = 0; q1 < NQ; ++q1) a += T(p1[q1]) * T(ps[(q1 + NQ * q2) * 4]);
-        acc += T(p2[q2]) * a;
-      }
-      s_psi[tid] = acc;
-    }
+    if (en >= 0) s_psi[tid] = T(psi_face_node<NP, NQ>(M, en, 2 + (1 - s), k % NP, k / NP));
   }
   phase();
 

@@ -2081,14 +2081,17 @@ bool velocity_l1_supported(int np, int nq, int nqy) {
 
 const char* velocity_l1_combos() { return "(3,4,8) (4,4,8) (4,5,8) (5,7,8)"; }
 
-// Cells next to an enriched layer and enriched cells; the other cells take
-// launch_viscous_regular.
+// Enriched cells and, with degree-1 weights, the cells next to them; the other
+// cells take launch_viscous_regular.
 template <int NP, int NQ, int NQW, int LE>
 static int launch_visc_ms_t(const dg_mesh* m, const MeshDev& M, const RegularLayers& L, const double* u, double* r,
                             hipStream_t s) {
-  if (L.xnl > 0)
-    hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQ, false, LE>), dim3((unsigned)((int64_t)m->P.nx * L.xnl * m->P.nz)),
-                       dim3(256), 0, s, M, u, r, L.xlo, L.xnl, L.xstep);
+  if constexpr (LE != 1) {
+    if (L.xnl > 0)
+      hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQ, false, LE>),
+                         dim3((unsigned)((int64_t)m->P.nx * L.xnl * m->P.nz)), dim3(256), 0, s, M, u, r, L.xlo, L.xnl,
+                         L.xstep);
+  }
   if (m->nenr > 0)
     hipLaunchKernelGGL((visc_ms_kernel<NP, NQ, NQW, true, LE>), dim3((unsigned)m->nenr), dim3(256), 0, s, M, u, r, 0,
                        0, 1);
@@ -2100,7 +2103,8 @@ int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double*
   MeshDev M = velocity_meshdev(m);
   M.nut = nut;
   const RegularLayers L = regular_layers(m);
-  int rc = launch_viscous_regular(m, u, out, L.ilo, L.inl, inverse_mass, s);
+  int rc = m->nle == 1 ? launch_viscous_regular(m, u, out, L.lo, L.nl, inverse_mass, s)
+                       : launch_viscous_regular(m, u, out, L.ilo, L.inl, inverse_mass, s);
   if (rc || m->nenr == 0) return rc;
   const int np = m->np_u, nq = m->P.nq_u, nqw = m->P.nq_wn;
   bool done = false;
@@ -2123,7 +2127,7 @@ int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double*
 #undef X
     if (!done) return set_error(DG_ERR_UNSUPPORTED, "velocity degree/quadrature combination not compiled");
   }
-  if (!rc && inverse_mass) rc = launch_inverse_mass_layers(m, out, out, L.xlo, L.xnl, L.xstep, s);
+  if (!rc && inverse_mass) rc = launch_inverse_mass_layers(m, out, out, L.xlo, m->nle == 1 ? 0 : L.xnl, L.xstep, s);
   return rc;
 }
 
