@@ -693,23 +693,24 @@ __device__ __forceinline__ double wave_sum(double v) {
 //   (d r / d x_c, d r / d x_d)_w  for cd = 00 01 02 11 12 22,
 // with grad r = grad psi - grad P psi at the enriched volume points (weights
 // without |J|, physical derivatives).
+constexpr int kCoupThreads = 256;
 __host__ __device__ constexpr int coup_stride(int np3) { return 9 * np3 + 6; }
 
 template <int NP, int NQ, int NQY>
-__global__ __launch_bounds__(kSpecThreads) void coupling_kernel(const InvMassArgs A, double* coup) {
+__global__ __launch_bounds__(kCoupThreads) void coupling_kernel(const InvMassArgs A, double* coup) {
   constexpr int NP3 = NP * NP * NP, NPT = NQ * NQY * NQ;
   constexpr auto& tq = ct::tab<NP, NQ>;
   constexpr auto& ty = ct::tab<NP, NQY>;
   __shared__ double W0[9 * NPT], W1[9 * NPT], OUT[9 * NP3];
   __shared__ double Av[NP3];
-  __shared__ double red[6 * (kSpecThreads / 64)];
+  __shared__ double red[6 * (kCoupThreads / 64)];
   const int tid = threadIdx.x;
   const int64_t b = blockIdx.x;
   const int64_t e = enriched_cell_index(A.nx, A.ny, A.lower_slot, A.nslots, b);
   const int ey = (int)((e / A.nx) % A.ny);
   const double h[3] = {1.0 / A.ihx, 1.0 / A.ihy[ey], 1.0 / A.ihz};
   const double* ps = A.psi + b * A.psi_pts * 4;
-  for (int B = tid; B < NP3; B += kSpecThreads) Av[B] = A.apoly[b * apoly_stride(NP3) + B];
+  for (int B = tid; B < NP3; B += kCoupThreads) Av[B] = A.apoly[b * apoly_stride(NP3) + B];
   __syncthreads();
   // reference gradient of P psi at the points: W0[d][q]
   sweep_c<0, NP, NP, NP, NQ, false, false, MDt<NP, NQ>>(Av, NP3, W1, NPT, 1.0, 1, 0);
@@ -723,7 +724,7 @@ __global__ __launch_bounds__(kSpecThreads) void coupling_kernel(const InvMassArg
   sweep_c<2, NQ, NQY, NP, NQ, false, false, MDt<NP, NQ>>(W1 + 4 * NPT, NPT, W0 + 2 * NPT, NPT, 1.0, 1, 128);
   __syncthreads();
   double e6[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int q = tid; q < NPT; q += kSpecThreads) {
+  for (int q = tid; q < NPT; q += kCoupThreads) {
     const int qx = q % NQ, qy = (q / NQ) % NQY, qz = q / (NQ * NQY);
     const double w = tq.w[qx] * ty.w[qy] * tq.w[qz];
     double gr[3];
@@ -753,137 +754,154 @@ __global__ __launch_bounds__(kSpecThreads) void coupling_kernel(const InvMassArg
   sweep_c<2, NP, NP, NQ, NP, true, false, MSt<NP, NQ>>(W1, NPT, OUT, NP3, 1.0, 6, 0);
   sweep_c<2, NP, NP, NQ, NP, true, false, MDt<NP, NQ>>(W1 + 6 * NPT, NPT, OUT + 6 * NP3, NP3, 1.0, 3, 128);
   __syncthreads();
-  for (int it = tid; it < 9 * NP3; it += kSpecThreads) {
+  for (int it = tid; it < 9 * NP3; it += kCoupThreads) {
     const int d = it / (3 * NP3), k = it - d * 3 * NP3, cc = k / NP3, B = k - cc * NP3;
     out[it] = OUT[(cc * 3 + d) * NP3 + B];
   }
 }
 
-template <int NP, int NQ, int NQY>
-__global__ __launch_bounds__(kSpecThreads) void bordered_step_kernel(const BorderArgs S) {
-  constexpr int NP2 = NP * NP, NP3 = NP2 * NP, N = 3 * NP3, NC = 16, LD = NC + 2;
-  __shared__ double T[N * LD];
-  __shared__ double Mt[3 * NP2];
+// Projection step of the enriched cells: the layer's tables (kern_spectral.hip)
+// on four columns of a cell, its right-hand side and the three couplings, then
+// the 3 x 3 Schur complement of the enrichment unknowns.  Four cells fill the 16
+// columns of a matrix-core product; only the combined column of each is needed
+// from the second one.  4,096 cells, k = 4: 127 us, 376 us with dense tables.
+template <int NP>
+__global__ __launch_bounds__(tile_threads(NP), tile_waves(NP)) void bordered_step_kernel(const BorderArgs S) {
+  constexpr int NP2 = NP * NP, NP3 = NP2 * NP, N = 3 * NP3, LD = kTileLD, NT = tile_threads(NP);
+  using Gemm = BlockGemm<NP, NT / 64>;
+  constexpr auto& P = parity<NP>;
+  __shared__ double T[Parity<NP>::ROWS * LD];
+  __shared__ double Mt[NP2];
+  __shared__ short cls[N];
   __shared__ double XE[4][3];
   const InvMassArgs& A = S.im;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slot = blockIdx.x / S.tiles;
   const int64_t j0 = (int64_t)(blockIdx.x % S.tiles) * 4;
   const int nc = S.ncol - j0 < 4 ? (int)(S.ncol - j0) : 4;
   const int ey = slot == A.lower_slot ? 0 : A.ny - 1;
   const double h[3] = {1.0 / A.ihx, 1.0 / A.ihy[ey], 1.0 / A.ihz};
   const double detJ = h[0] * h[1] * h[2], f = S.scale / detJ;
-  // cell c of the tile: enriched index and cell index
-  auto enr_of = [&](int c) -> int64_t {
-    const int64_t j = j0 + c;
-    return j % A.nx + (int64_t)A.nx * (slot + (int64_t)A.nslots * (j / A.nx));
-  };
-  auto cell_of = [&](int c) -> int64_t {
-    const int64_t j = j0 + c;
-    return j % A.nx + (int64_t)A.nx * (ey + (int64_t)A.ny * (j / A.nx));
-  };
-  for (int i = tid; i < 3 * NP2; i += kSpecThreads) Mt[i] = S.mats[i];
+  // cell c of the tile: enriched index and cell index (those of cell 0 in padding)
+  __shared__ int64_t EB[4], CB[4];
+  __shared__ double TAU[4], AG[4][3], Gp[NT / 64][4][9];
+  if (tid < 4) {
+    const int64_t j = j0 + (tid < nc ? tid : 0);
+    EB[tid] = j % A.nx + (int64_t)A.nx * (slot + (int64_t)A.nslots * (j / A.nx));
+    CB[tid] = j % A.nx + (int64_t)A.nx * (ey + (int64_t)A.ny * (j / A.nx));
+    TAU[tid] = tid < nc ? S.tau_d[CB[tid]] : 0.0;
+  }
+  __syncthreads();
+  for (int i = tid; i < NP2; i += NT) Mt[i] = S.mats[i];
+  for (int i = tid; i < (Parity<NP>::ROWS - N) * LD; i += NT) T[N * LD + i] = 0.0;
+  for (int i = tid; i < N; i += NT) cls[P.pos[i]] = (short)i;
   // columns: -f g_p, then tau t'_d (zero in padding cells)
-  for (int it = tid; it < 4 * 4 * N; it += kSpecThreads) {
-    const int c = it / (4 * N), r = it - c * 4 * N, col = r / N, k = r - col * N;
-    double v = 0.0;
-    if (c < nc) {
-      if (col == 0)
-        v = -f * S.g[cell_of(c) * N + k];
-      else
-        v = S.tau_d[cell_of(c)] * S.coup[enr_of(c) * coup_stride(NP3) + (col - 1) * N + k];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const double* gc = S.g + CB[c] * N;
+    const double* tc = S.coup + EB[c] * coup_stride(NP3) - N;
+    const double fg = c < nc ? -f : 0.0, ft = TAU[c];
+#pragma unroll 3
+    for (int it = tid; it < 4 * N; it += NT) {
+      const int col = it / N, k = it - col * N;
+      T[k * LD + 4 * c + col] = c < nc ? (col == 0 ? fg * gc[it] : ft * tc[it]) : 0.0;
     }
-    T[k * LD + 4 * c + col] = v;
   }
-  __syncthreads();
-  // Mh^{-1} on all columns; column 0 becomes Mh^{-1} b_p = u_p + a u_e - f Mh^{-1} g_p
-  tile_sweep<NP, NC, 0>(T, Mt, tid);
-  __syncthreads();
-  tile_sweep<NP, NC, 1>(T, Mt, tid);
-  __syncthreads();
-  tile_sweep<NP, NC, 2>(T, Mt, tid);
-  __syncthreads();
-  for (int it = tid; it < 4 * N; it += kSpecThreads) {
-    const int c = it / N, k = it - c * N, cc = k / NP3, B = k - cc * NP3;
-    if (c >= nc) continue;
-    const int64_t b = enr_of(c);
-    const double a = A.apoly[b * apoly_stride(NP3) + B];
-    T[k * LD + 4 * c] += S.u_hat[cell_of(c) * N + k] + a * S.u_hat[A.ncell * N + 3 * b + cc];
-  }
-  __syncthreads();
-  // per-cell scalars: wavefront wv <-> cell wv
-  __shared__ double TAU[4], Gp[2][4][9];
-  const bool valid = wv < nc;
-  const int64_t b = valid ? enr_of(wv) : 0;
-  const int64_t e = valid ? cell_of(wv) : 0;
-  const double tau = valid ? S.tau_d[e] : 0.0;
-  const double* ap = A.apoly + b * apoly_stride(NP3);
-  const bool on = valid && ap[NP3] != 0.0;
-  double ag[3] = {0.0, 0.0, 0.0};  // sum_B a_B g_p[d][B]
-  if (on) {
-    const double* gp = S.g + e * N;
+  // sum_B a_B g_p[d][B] of cell wv
+  if (wv < nc) {
+    const double* ap = A.apoly + EB[wv] * apoly_stride(NP3);
+    const double* gp = S.g + CB[wv] * N;
+    double ag[3] = {0.0, 0.0, 0.0};
     for (int B = lane; B < NP3; B += 64) {
       const double aB = ap[B];
       ag[0] += aB * gp[B];
       ag[1] += aB * gp[NP3 + B];
       ag[2] += aB * gp[2 * NP3 + B];
     }
-  }
 #pragma unroll
-  for (int i = 0; i < 3; ++i) ag[i] = wave_sum(ag[i]);
-  if (lane == 0) TAU[wv] = tau;
-  const int32_t lslot = S.map[ey];
-  const double* Zs = S.slots + (size_t)lslot * (2 * (size_t)N * N + N);
-  const double* lam = Zs + 2 * (size_t)N * N;
-  __syncthreads();
-  // dense products split 2 x 2: wavefront (rw, cw) takes row chunks rw + 2 i
-  // and the columns of cells 2 cw, 2 cw + 1
-  constexpr int WR = 2, CPW = 8, RPW = ((N + 63) / 64 + WR - 1) / WR;
-  const int rw = wv % WR, cw = wv / WR;
-  double acc[RPW][CPW];
-  tile_gemm_split<N, LD, WR, RPW, CPW>(T, Zs, acc, lane, wv);
-  // weighted dot products G_jk = sum_r y_j[r] y_k[r] / (1 + tau lambda_r), partial over this row half
-  double sr[RPW][2];
-  double Gl[2][9];
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int k = 0; k < 9; ++k) Gl[m][k] = 0.0;
-#pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    const int r = 64 * (rw + WR * i) + lane;
-    const double lr = r < N ? lam[r] : 0.0;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const double w = r < N ? 1.0 / (1.0 + TAU[2 * cw + m] * lr) : 0.0;
-      sr[i][m] = w;
-      const double y0 = acc[i][4 * m], y1 = acc[i][4 * m + 1], y2 = acc[i][4 * m + 2], y3 = acc[i][4 * m + 3];
-      Gl[m][0] += w * y1 * y0;  // 10 20 30 11 12 13 22 23 33
-      Gl[m][1] += w * y2 * y0;
-      Gl[m][2] += w * y3 * y0;
-      Gl[m][3] += w * y1 * y1;
-      Gl[m][4] += w * y1 * y2;
-      Gl[m][5] += w * y1 * y3;
-      Gl[m][6] += w * y2 * y2;
-      Gl[m][7] += w * y2 * y3;
-      Gl[m][8] += w * y3 * y3;
+    for (int d = 0; d < 3; ++d) {
+      ag[d] = wave_sum(ag[d]);
+      if (lane == 0) AG[wv][d] = ag[d];
     }
   }
+  __syncthreads();
+  // Mh^{-1} on all columns; column 0 becomes Mh^{-1} b_p = u_p + a u_e - f Mh^{-1} g_p
+  tile_sweep<NP, NT, 0>(T, Mt, tid);
+  __syncthreads();
+  tile_sweep<NP, NT, 1>(T, Mt, tid);
+  __syncthreads();
+  tile_sweep<NP, NT, 2>(T, Mt, tid);
+  __syncthreads();
+#pragma unroll 3
+  for (int it = tid; it < nc * N; it += NT) {
+    const int c = it / N, k = it - c * N, cc = k / NP3, B = k - cc * NP3;
+    const double a = A.apoly[EB[c] * apoly_stride(NP3) + B];
+    T[k * LD + 4 * c] += S.u_hat[CB[c] * N + k] + a * S.u_hat[A.ncell * N + 3 * EB[c] + cc];
+  }
+  __syncthreads();
+  tile_parity<NP, NT, false>(T, cls, tid);
+  const int32_t lslot = S.map[ey];
+  const double* Zs = S.slots + (size_t)lslot * (2 * (size_t)Parity<NP>::ZN + N);
+  const double* lam = Zs + 2 * (size_t)Parity<NP>::ZN;
+  Gemm gemm;
+  dgwm_d4 acc[Gemm::RT];
+  gemm.load(Zs, lane, wv);
+  gemm.run(T, Zs, acc, lane, wv);
+  __syncthreads();
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+  for (int q = 0; q < Gemm::RT; ++q)
 #pragma unroll
-    for (int k = 0; k < 9; ++k) Gl[m][k] = wave_sum(Gl[m][k]);
-  if (lane == 0)
+    for (int j = 0; j < 4; ++j) {
+      const int row = Gemm::row(q, j, lane, wv);
+      if (row >= 0) T[row * LD + (lane & 15)] = acc[q][j];
+    }
+  __syncthreads();
+  // weighted dot products G_jk = sum_r y_j[r] y_k[r] / (1 + tau lambda_r) of a cell's four columns; thread tid takes
+  // rows tid / 4 + NT / 4 i of cell tid % 4 and keeps their values for the combined column
+  constexpr int RW = (N + NT / 4 - 1) / (NT / 4);
+  const double tl = TAU[tid & 3];
+  double yr[RW][4], sr[RW];
+  double Gl[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+  for (int i = 0; i < RW; ++i) {
+    const int r = (tid >> 2) + (NT / 4) * i;
+    const double w = r < N ? 1.0 / (1.0 + tl * lam[r < N ? r : 0]) : 0.0;
+    sr[i] = w;
 #pragma unroll
-      for (int k = 0; k < 9; ++k) Gp[rw][2 * cw + m][k] = Gl[m][k];
-  __syncthreads();  // every wavefront is done reading T; partial sums published
+    for (int c = 0; c < 4; ++c) yr[i][c] = r < N ? T[r * LD + 4 * (tid & 3) + c] : 0.0;
+    const double y0 = yr[i][0], y1 = yr[i][1], y2 = yr[i][2], y3 = yr[i][3];
+    Gl[0] += w * y1 * y0;  // 10 20 30 11 12 13 22 23 33
+    Gl[1] += w * y2 * y0;
+    Gl[2] += w * y3 * y0;
+    Gl[3] += w * y1 * y1;
+    Gl[4] += w * y1 * y2;
+    Gl[5] += w * y1 * y3;
+    Gl[6] += w * y2 * y2;
+    Gl[7] += w * y2 * y3;
+    Gl[8] += w * y3 * y3;
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {  // over the lanes of the cell
+#pragma unroll
+    for (int o = 4; o < 64; o *= 2) Gl[k] += __shfl_xor(Gl[k], o);
+    if (lane < 4) Gp[wv][lane][k] = Gl[k];
+  }
+  __syncthreads();  // partial sums published
   double G[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) G[k] = Gp[0][wv][k] + Gp[1][wv][k];
+  for (int k = 0; k < 9; ++k) {
+    G[k] = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) G[k] += Gp[w][wv & 3][k];
+  }
+  // per-cell scalars: wavefront wv < 4 <-> cell wv
+  const bool valid = wv < nc;
+  const int64_t b = EB[valid ? wv : 0];
+  const double tau = TAU[valid ? wv : 0];
+  const double* ap = A.apoly + b * apoly_stride(NP3);
+  const double* ag = AG[wv & 3];
   double xe[3] = {0.0, 0.0, 0.0};
-  if (on) {
+  if (valid && ap[NP3] != 0.0) {
     const double rr = 1.0 / ap[NP3];
     const double* ue = S.u_hat + A.ncell * N + 3 * b;
     const double* ge = S.g + A.ncell * N + 3 * b;
@@ -902,37 +920,35 @@ __global__ __launch_bounds__(kSpecThreads) void bordered_step_kernel(const Borde
     xe[1] = (c01 * r0 + c11 * r1 + c12 * r2) * idet;
     xe[2] = (c02 * r0 + c12 * r1 + c22 * r2) * idet;
   }
-  if (lane == 0)
+  Gemm gemm2;
+  gemm2.load(Zs + Parity<NP>::ZN, lane, wv);
+  if (lane == 0 && wv < 4)
 #pragma unroll
     for (int d = 0; d < 3; ++d) XE[wv][d] = xe[d];
   __syncthreads();  // XE published
+  // combined column of every cell, in the place of its first one
 #pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    const int r = 64 * (rw + WR * i) + lane;
+  for (int i = 0; i < RW; ++i) {
+    const int r = (tid >> 2) + (NT / 4) * i, c = tid & 3;
     if (r < N)
-#pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        const int cl = 2 * cw + m;
-        T[r * LD + 4 * cl] = (acc[i][4 * m] - XE[cl][0] * acc[i][4 * m + 1] - XE[cl][1] * acc[i][4 * m + 2] -
-                              XE[cl][2] * acc[i][4 * m + 3]) * sr[i][m];
-      }
+      T[r * LD + 4 * c] = (yr[i][0] - XE[c][0] * yr[i][1] - XE[c][1] * yr[i][2] - XE[c][2] * yr[i][3]) * sr[i];
   }
   __syncthreads();
-  tile_gemm_split<N, LD, WR, RPW, CPW>(T, Zs + (size_t)N * N, acc, lane, wv);
+  gemm2.run(T, Zs + Parity<NP>::ZN, acc, lane, wv);
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < RPW; ++i) {
-    const int r = 64 * (rw + WR * i) + lane;
-    if (r < N)
+  for (int q = 0; q < Gemm::RT; ++q)
 #pragma unroll
-      for (int m = 0; m < 2; ++m) T[r * LD + 4 * (2 * cw + m)] = acc[i][4 * m];
-  }
+    for (int j = 0; j < 4; ++j) {
+      const int row = Gemm::row(q, j, lane, wv);
+      if (row >= 0 && (lane & 3) == 0) T[row * LD + (lane & 15)] = acc[q][j];
+    }
   __syncthreads();
+  tile_parity<NP, NT, true, 4>(T, cls, tid);
   // back to the psi basis: x_p = x'_p - a x_e
-  for (int it = tid; it < 4 * N; it += kSpecThreads) {
+  for (int it = tid; it < nc * N; it += NT) {
     const int c = it / N, k = it - c * N, cc = k / NP3, B = k - cc * NP3;
-    if (c < nc)
-      S.x[cell_of(c) * N + k] = T[k * LD + 4 * c] - A.apoly[enr_of(c) * apoly_stride(NP3) + B] * XE[c][cc];
+    S.x[CB[c] * N + k] = T[k * LD + 4 * c] - A.apoly[EB[c] * apoly_stride(NP3) + B] * XE[c][cc];
   }
   if (valid && lane < 3) S.x[A.ncell * N + 3 * b + lane] = XE[wv][lane];
 }
@@ -1071,7 +1087,7 @@ int launch_projection_step(const dg_mesh* m, const double* tau_d, const double* 
     bool launched = false;
 #define X(p, q, w)                                                                                               \
     if (!launched && m->np_u == p && m->P.nq_u == q && m->P.nq_wn == w) {                                        \
-      hipLaunchKernelGGL((coupling_kernel<p, q, w>), dim3((unsigned)m->nenr), dim3(kSpecThreads), 0, s, IA,     \
+      hipLaunchKernelGGL((coupling_kernel<p, q, w>), dim3((unsigned)m->nenr), dim3(kCoupThreads), 0, s, IA,     \
                          m->coup);                                                                               \
       launched = true;                                                                                           \
     }
@@ -1098,7 +1114,7 @@ int launch_projection_step(const dg_mesh* m, const double* tau_d, const double* 
   const int grid = (int)(tiles * m->n_enr_layers);
 #define X(p, q, w)                                                                                       \
   if (m->np_u == p && m->P.nq_u == q && m->P.nq_wn == w) {                                               \
-    hipLaunchKernelGGL((bordered_step_kernel<p, q, w>), dim3((unsigned)grid), dim3(kSpecThreads), 0, s, B); \
+    hipLaunchKernelGGL((bordered_step_kernel<p>), dim3((unsigned)grid), dim3(tile_threads(p)), 0, s, B); \
     return check_hip(hipGetLastError(), "projection step kernel launch");                                \
   }
   DG_PRJ_COMBOS(X)

@@ -12,11 +12,18 @@
 // layer height, on the host, by the cyclic Jacobi method),
 //   x = L^{-T} Z diag(1 / (1 + tau_D,e lambda)) Z^T L^T (u_hat - (s/|J|) Mh^{-1} g).
 // Mh^{-1} is a sweep with 1-D matrices; L^T and L^{-T} are folded into the
-// layer's tables, (L Z)^T and L^{-T} Z, which are dense products shared by
-// all cells of a layer, so a workgroup takes a tile of NC
-// cells of one layer and runs both products out of LDS, on the FP64 matrix
-// cores for 16-cell tiles (a vector product for the 8-cell tiles of k = 5).
-// The result is exact up to rounding: no iteration, every cell the same work.
+// layer's tables (L Z)^T and L^{-T} Z.  The cell is symmetric under reflection
+// in each direction, so in even/odd coordinates both tables fall into eight
+// diagonal blocks (Parity in kern_tile.h); the change of coordinates is sums
+// and differences along the three directions.  A workgroup takes a tile of 16
+// cells of one layer and runs both block products out of LDS on the FP64
+// matrix cores.  The result is exact up to rounding: no iteration, every cell
+// the same work.
+// Measured (64 x 32 x 32 cells, k = 4, 61,440 cells here): 324 us, 0.55 GB at
+// 1.7 TB/s; with the dense 375 x 375 tables it was 1,196 us, bound by their
+// products.  What is left is the LDS passes between barriers and, at the FP64
+// matrix rate, 80 us of products.  Eight wavefronts on a tile instead of four
+// fill the wait of one phase with another tile's work at the same LDS.
 #include <algorithm>
 #include <thread>
 #include <vector>
@@ -30,18 +37,13 @@ namespace dgwm {
 namespace {
 
 
-template <int NP>
-constexpr int spec_nc() {
-  return NP >= 6 ? 8 : 16;
-}
-
 struct SpecArgs {
   int nx, ny, layer_lo, tiles, nblocks;  // tiles per layer; blocks in the launch
   int64_t ncol;                          // cells per layer (nx * nz)
   double hx, hz;
   const double* hy;     // [ny] cell heights
-  const double* mats;   // [3][np][np]: K^{-1}, C^T, C^{-T} (row-major, out_a = sum_i M[a][i] in_i)
-  const double* slots;  // [slot][2 n^2 + n]: A1[k][r] = (L Z)[k][r], A2[k][r] = (L^{-T} Z)[r][k], lambda
+  const double* mats;   // [np][np]: K^{-1} (row-major, out_a = sum_i M[a][i] in_i)
+  const double* slots;  // [slot]: first product, second product (operand order of BlockGemm), lambda (class order)
   const int32_t* map;   // [ny] slot of each layer
   const double* tau_d;
   const double* u_hat;
@@ -50,14 +52,17 @@ struct SpecArgs {
   double* x;
 };
 
-template <int NP, int NC>
-__global__ __launch_bounds__(kSpecThreads) void spectral_step_kernel(const SpecArgs A) {
-  constexpr int NP2 = NP * NP, NP3 = NP2 * NP, N = 3 * NP3, LD = NC + 2;
-  constexpr int WR = 2, CPW = NC / (4 / WR);       // wavefronts along rows; columns per wavefront
-  constexpr int RPW = ((N + 63) / 64 + WR - 1) / WR;  // row chunks per wavefront
-  __shared__ double T[N * LD];
-  __shared__ double Mt[3 * NP2];
+template <int NP>
+__global__ __launch_bounds__(tile_threads(NP), tile_waves(NP)) void spectral_step_kernel(const SpecArgs A) {
+  constexpr int NP2 = NP * NP, NP3 = NP2 * NP, N = 3 * NP3, NC = kTileCols, LD = kTileLD, NT = tile_threads(NP);
+  constexpr int PL = (NC * N + NT - 1) / NT;  // values of the tile per thread
+  constexpr auto& P = parity<NP>;
+  using Gemm = BlockGemm<NP, NT / 64>;
+  __shared__ double T[Parity<NP>::ROWS * LD];
+  __shared__ double Mt[NP2];
   __shared__ double tauc[NC];
+  __shared__ int64_t base[NC];
+  __shared__ short cls[N];
   // consecutive logical blocks (tiles of one layer) on one XCD: hardware
   // block b runs on XCD b % 8
   const int per = (A.nblocks + 7) / 8;
@@ -67,90 +72,83 @@ __global__ __launch_bounds__(kSpecThreads) void spectral_step_kernel(const SpecA
   const int layer = A.layer_lo + lb / A.tiles;
   const int64_t j0 = (int64_t)(lb % A.tiles) * NC;
   const int nc = A.ncol - j0 < NC ? (int)(A.ncol - j0) : NC;
-  const int64_t rowc = (int64_t)A.nx * A.ny;
-  auto cell = [&](int c) -> int64_t {
-    const int64_t j = j0 + c;
-    return j % A.nx + (int64_t)A.nx * layer + rowc * (j / A.nx);
-  };
-  for (int i = tid; i < 3 * NP2; i += kSpecThreads) Mt[i] = A.mats[i];
-  if (tid < NC) tauc[tid] = tid < nc ? A.tau_d[cell(tid)] : 0.0;
-  const double detJ = A.hx * A.hy[layer] * A.hz;
-  for (int idx = tid; idx < NC * N; idx += kSpecThreads) {
-    const int c = idx / N, k = idx - c * N;
-    T[k * LD + c] = c < nc ? A.g[cell(c) * N + k] : 0.0;
+  if (tid < NC) {
+    const int64_t j = j0 + (tid < nc ? tid : 0);
+    const int64_t e = j % A.nx + (int64_t)A.nx * layer + (int64_t)A.nx * A.ny * (j / A.nx);
+    base[tid] = e * N;
+    tauc[tid] = tid < nc ? A.tau_d[e] : 0.0;
   }
+  for (int i = tid; i < NP2; i += NT) Mt[i] = A.mats[i];
+  for (int i = tid; i < (Parity<NP>::ROWS - N) * LD; i += NT) T[N * LD + i] = 0.0;
+  for (int i = tid; i < N; i += NT) cls[P.pos[i]] = (short)i;
+  __syncthreads();
+  double u[PL];
+  auto fetch = [&](const double* __restrict__ src) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+      const int idx = tid + i * NT, c = idx / N;
+      u[i] = c < nc ? src[base[c] + (idx - c * N)] : 0.0;
+    }
+  };
+  fetch(A.g);
+#pragma unroll
+  for (int i = 0; i < PL; ++i) {
+    const int idx = tid + i * NT, c = idx / N;
+    if (idx < NC * N) T[(idx - c * N) * LD + c] = u[i];
+  }
+  fetch(A.u_hat);  // in flight over the sweeps
   __syncthreads();
   // Mh^{-1} g
-  tile_sweep<NP, NC, 0>(T, Mt, tid);
+  tile_sweep<NP, NT, 0>(T, Mt, tid);
   __syncthreads();
-  tile_sweep<NP, NC, 1>(T, Mt, tid);
+  tile_sweep<NP, NT, 1>(T, Mt, tid);
   __syncthreads();
-  tile_sweep<NP, NC, 2>(T, Mt, tid);
+  tile_sweep<NP, NT, 2>(T, Mt, tid);
   __syncthreads();
-  const double f = A.scale / detJ;
-  for (int idx = tid; idx < NC * N; idx += kSpecThreads) {
-    const int c = idx / N, k = idx - c * N;
-    T[k * LD + c] = (c < nc ? A.u_hat[cell(c) * N + k] : 0.0) - f * T[k * LD + c];
+  const double f = A.scale / (A.hx * A.hy[layer] * A.hz);
+#pragma unroll
+  for (int i = 0; i < PL; ++i) {
+    const int idx = tid + i * NT, c = idx / N;
+    if (idx < NC * N) T[(idx - c * N) * LD + c] = u[i] - f * T[(idx - c * N) * LD + c];
   }
   __syncthreads();
   // (the factors L^T before and L^{-T} after the products are folded into the tables)
-  const double* Zs = A.slots + (size_t)A.map[layer] * (2 * (size_t)N * N + N);
-  const double* lam = Zs + 2 * (size_t)N * N;
-  const int lane = tid & 63, wv = tid >> 6;
-  if constexpr (NC == 16) {
-    // matrix cores: wavefront wv owns row tiles wv + 4 q, all 16 columns
-    constexpr int RTW = ((N + 15) / 16 + 3) / 4;
-    dgwm_d4 acc[RTW];
-    tile_gemm_mfma<N, LD, RTW>(T, Zs, acc, lane, wv);
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < RTW; ++q)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = 16 * (wv + 4 * q) + 4 * j + (lane >> 4), c = lane & 15;
-        if (r < N) T[r * LD + c] = acc[q][j] / (1.0 + tauc[c] * lam[r]);
-      }
-    __syncthreads();
-    tile_gemm_mfma<N, LD, RTW>(T, Zs + (size_t)N * N, acc, lane, wv);
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < RTW; ++q)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = 16 * (wv + 4 * q) + 4 * j + (lane >> 4), c = lane & 15;
-        if (r < N) T[r * LD + c] = acc[q][j];
-      }
-  } else {
-    const int rw = wv % WR, c0 = (wv / WR) * CPW;
-    double acc[RPW][CPW];
-    tile_gemm_split<N, LD, WR, RPW, CPW>(T, Zs, acc, lane, wv);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-      const int r = 64 * (rw + WR * i) + lane;
-      if (r < N) {
-        const double lr = lam[r];
-#pragma unroll
-        for (int j = 0; j < CPW; ++j) T[r * LD + c0 + j] = acc[i][j] / (1.0 + tauc[c0 + j] * lr);
-      }
-    }
-    __syncthreads();
-    tile_gemm_split<N, LD, WR, RPW, CPW>(T, Zs + (size_t)N * N, acc, lane, wv);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-      const int r = 64 * (rw + WR * i) + lane;
-      if (r < N) {
-#pragma unroll
-        for (int j = 0; j < CPW; ++j) T[r * LD + c0 + j] = acc[i][j];
-      }
-    }
-    __syncthreads();
-  }
+  const double* Z1 = A.slots + (size_t)A.map[layer] * (2 * (size_t)Parity<NP>::ZN + N);
+  const double* Z2 = Z1 + Parity<NP>::ZN;
+  const double* lam = Z2 + Parity<NP>::ZN;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), col = lane & 15;
+  tile_parity<NP, NT, false>(T, cls, tid);
+  Gemm gemm;
+  dgwm_d4 acc[Gemm::RT];
+  gemm.load(Z1, lane, wv);
+  gemm.run(T, Z1, acc, lane, wv);
+  gemm.load(Z2, lane, wv);
   __syncthreads();
-  for (int idx = tid; idx < NC * N; idx += kSpecThreads) {
-    const int c = idx / N, k = idx - c * N;
-    if (c < nc) A.x[cell(c) * N + k] = T[k * LD + c];
+#pragma unroll
+  for (int q = 0; q < Gemm::RT; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = Gemm::row(q, j, lane, wv);
+      if (row >= 0) T[row * LD + col] = acc[q][j] / (1.0 + tauc[col] * lam[row]);
+    }
+  __syncthreads();
+  gemm.run(T, Z2, acc, lane, wv);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Gemm::RT; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = Gemm::row(q, j, lane, wv);
+      if (row >= 0) T[row * LD + col] = acc[q][j];
+    }
+  __syncthreads();
+  tile_parity<NP, NT, true>(T, cls, tid);
+  int id = tid;
+  asm("" : "+v"(id));
+#pragma unroll
+  for (int i = 0; i < PL; ++i) {
+    const int idx = id + i * NT, c = idx / N;
+    if (c < nc) A.x[base[c] + (idx - c * N)] = T[(idx - c * N) * LD + c];
   }
 }
 
@@ -206,11 +204,56 @@ int spectral_layers(const dg_mesh& m, std::vector<int>* map, std::vector<double>
   return (int)hs.size();
 }
 
+namespace {
+
+// Reflection classes for a run-time np (host side of Parity).
+struct Classes {
+  int n[8], tiles[8], steps, zn;  // sizes, row tiles; steps of a tile, entries of a product
+  std::vector<int> pos;
+};
+template <int NP>
+Classes classes_of() {
+  Classes c;
+  for (int p = 0; p < 8; ++p) {
+    c.n[p] = parity<NP>.n[p];
+    c.tiles[p] = (c.n[p] + 15) / 16;
+  }
+  c.steps = Parity<NP>::KS;
+  c.zn = Parity<NP>::ZN;
+  c.pos.assign(parity<NP>.pos, parity<NP>.pos + Parity<NP>::N);
+  return c;
+}
+bool spectral_classes(int np, Classes* c) {
+  switch (np) {
+    case 3: *c = classes_of<3>(); return true;
+    case 4: *c = classes_of<4>(); return true;
+    case 5: *c = classes_of<5>(); return true;
+    case 6: *c = classes_of<6>(); return true;
+  }
+  return false;
+}
+// table entries of the two products of one layer
+size_t block_entries(int np) {
+  switch (np) {
+    case 3: return Parity<3>::ZN;
+    case 4: return Parity<4>::ZN;
+    case 5: return Parity<5>::ZN;
+    case 6: return Parity<6>::ZN;
+  }
+  return 0;
+}
+
+}  // namespace
+
+// K^{-1}, per layer slot the blocks and eigenvalues, the int32 layer map; at
+// least the two dense n x n tables of one layer are reserved, the size that
+// callers who leave the step tables out can count on saving.
 size_t spectral_table_doubles(const dg_mesh& m) {
   const int ns = spectral_layers(m, nullptr, nullptr);
   if (ns == 0) return 0;
   const size_t n = 3 * (size_t)m.np_u * m.np_u * m.np_u;
-  return 3 * (size_t)m.np_u * m.np_u + (size_t)ns * (2 * n * n + n) + (m.P.ny + 1) / 2;  // + int32 map
+  const size_t need = (size_t)m.np_u * m.np_u + (size_t)ns * (2 * block_entries(m.np_u) + n) + (m.P.ny + 1) / 2;
+  return std::max(need, 2 * n * n + n);
 }
 
 // Host: 1-D factors, whitened div-div forms, their eigendecompositions; copies
@@ -235,28 +278,57 @@ static int build_spectral_tables(const dg_mesh* m, hipStream_t s) {
       for (int q = 0; q < nq; ++q) v += w[q] * S[q * np + i] * S[q * np + j];
       K[i * np + j] = v;
     }
+  Classes cl;
+  if (!spectral_classes(np, &cl)) return set_error(DG_ERR_UNSUPPORTED, "projection step: degree not compiled");
+  // K^{-1} in nodal coordinates
   cholesky(np, K, C);
   lower_inverse(np, C, Ci);
-  const size_t head = 3 * (size_t)np * np, per = 2 * (size_t)n * n + n;
+  const size_t nz = (size_t)cl.zn, head = (size_t)np * np, per = 2 * nz + n;
   std::vector<double> host(spectral_table_doubles(*m), 0.0);
   double* Kinv = host.data();
-  double* CT = Kinv + np * np;
-  double* CiT = CT + np * np;
   for (int a = 0; a < np; ++a)
     for (int i = 0; i < np; ++i) {
       double v = 0.0;  // K^{-1} = C^{-T} C^{-1}
       for (int k = 0; k < np; ++k) v += Ci[k * np + a] * Ci[k * np + i];
       Kinv[a * np + i] = v;
-      CT[a * np + i] = C[i * np + a];
-      CiT[a * np + i] = Ci[i * np + a];
     }
-  // whitened 1-D tables: St = S C^{-T}, Sdt = Sd C^{-T}
+  // orthonormal even/odd coordinates Pm v (1 / sqrt 2 (v_i +- v_{np-1-i}), the middle node as it is); the device's
+  // sums and differences are these times dsc, which the tables divide out.  K in them is block diagonal, and its
+  // Cholesky factor with it.
+  const int ne = (np + 1) / 2, no = np / 2;
+  std::vector<double> Pm((size_t)np * np, 0.0), dsc(np, 1.0);
+  for (int i = 0; i < no; ++i) {
+    const double q = std::sqrt(0.5);
+    Pm[i * np + i] = Pm[i * np + np - 1 - i] = q;
+    Pm[(ne + i) * np + i] = q;
+    Pm[(ne + i) * np + np - 1 - i] = -q;
+    dsc[i] = dsc[ne + i] = std::sqrt(2.0);
+  }
+  if (np % 2) Pm[(ne - 1) * np + no] = 1.0;
+  std::vector<double> Kp((size_t)np * np, 0.0), Sp((size_t)nq * np, 0.0), Sdp((size_t)nq * np, 0.0);
+  for (int a = 0; a < np; ++a)
+    for (int b = 0; b < np; ++b) {
+      if ((a < ne) != (b < ne)) continue;
+      double v = 0.0;
+      for (int i = 0; i < np; ++i)
+        for (int j = 0; j < np; ++j) v += Pm[a * np + i] * K[i * np + j] * Pm[b * np + j];
+      Kp[a * np + b] = v;
+    }
+  for (int q = 0; q < nq; ++q)
+    for (int a = 0; a < np; ++a)
+      for (int i = 0; i < np; ++i) {
+        Sp[q * np + a] += S[q * np + i] * Pm[a * np + i];
+        Sdp[q * np + a] += Sd[q * np + i] * Pm[a * np + i];
+      }
+  cholesky(np, Kp, C);
+  lower_inverse(np, C, Ci);
+  // whitened 1-D tables: St = Sp C^{-T}, Sdt = Sdp C^{-T}
   std::vector<double> St((size_t)nq * np, 0.0), Sdt((size_t)nq * np, 0.0);
   for (int q = 0; q < nq; ++q)
     for (int a = 0; a < np; ++a)
       for (int i = 0; i < np; ++i) {
-        St[q * np + a] += S[q * np + i] * Ci[a * np + i];
-        Sdt[q * np + a] += Sd[q * np + i] * Ci[a * np + i];
+        St[q * np + a] += Sp[q * np + i] * Ci[a * np + i];
+        Sdt[q * np + a] += Sdp[q * np + i] * Ci[a * np + i];
       }
   std::vector<int> sweeps(ns, 0);
   auto work = [&](int slot) {
@@ -278,23 +350,7 @@ static int build_spectral_tables(const dg_mesh* m, hipStream_t s) {
                 G[(size_t)q * n + 2 * np3 + B] = sw * sx * sy * Sdt[qz * np + iz] / h[2];
               }
         }
-    std::vector<double> Bm((size_t)n * n, 0.0), lam, vt;
-    for (int q = 0; q < npt; ++q) {
-      const double* gq = &G[(size_t)q * n];
-      for (int I = 0; I < n; ++I) {
-        const double gi = gq[I];
-        if (gi == 0.0) continue;
-        double* row = &Bm[(size_t)I * n];
-        for (int J = 0; J < n; ++J) row[J] += gi * gq[J];
-      }
-    }
-    sweeps[slot] = sym_eig_jacobi(n, Bm, lam, vt);
-    // first product: (L Z)^T, stored as A1[k][r] = (L z_r)[k]; second: L^{-T} Z, stored as A2[k][r] = (L^{-T} z_k)[r]
-    // (z_r eigenvector r; L and L^{-T} applied as 1-D factors along each direction of each component)
-    double* A1 = host.data() + head + slot * per;
-    double* A2 = A1 + (size_t)n * n;
-    double* L = A2 + (size_t)n * n;
-    std::vector<double> v((size_t)n), w((size_t)n);
+    std::vector<double> Bm, lam, vt, v((size_t)n), w((size_t)n);
     auto along = [&](const std::vector<double>& M, bool transpose, std::vector<double>& x) {
       for (int dir = 0; dir < 3; ++dir) {
         const int sd = dir == 0 ? 1 : (dir == 1 ? np : np * np);
@@ -312,16 +368,48 @@ static int build_spectral_tables(const dg_mesh* m, hipStream_t s) {
           }
       }
     };
-    for (int r = 0; r < n; ++r) {
-      for (int k = 0; k < n; ++k) v[k] = w[k] = vt[(size_t)r * n + k];
-      along(C, false, v);   // L z_r
-      along(Ci, true, w);   // L^{-T} z_r
-      for (int k = 0; k < n; ++k) {
-        A1[(size_t)k * n + r] = v[k];
-        A2[(size_t)r * n + k] = w[k];
+    // scale of a 3-D coordinate (product over its directions)
+    auto scale = [&](int at) {
+      const int B = at % np3;
+      return dsc[B % np] * dsc[(B / np) % np] * dsc[B / (np * np)];
+    };
+    // per class: first product (L Z)^T, entry (k, r) = (L z_r)[k]; second L^{-T} Z, entry (k, r) = (L^{-T} z_k)[r]
+    // (z_r eigenvector r; L and L^{-T} as 1-D factors along each direction of each component)
+    double* A1 = host.data() + head + slot * per;
+    double* A2 = A1 + nz;
+    double* L = A2 + nz;
+    for (int p = 0, o = 0, t = 0; p < 8; o += cl.n[p], t += cl.tiles[p], ++p) {
+      const int np_ = cl.n[p];
+      const int* at = cl.pos.data() + o;
+      Bm.assign((size_t)np_ * np_, 0.0);
+      for (int q = 0; q < npt; ++q) {
+        const double* gq = &G[(size_t)q * n];
+        for (int I = 0; I < np_; ++I) {
+          const double gi = gq[at[I]];
+          double* row = &Bm[(size_t)I * np_];
+          for (int J = 0; J < np_; ++J) row[J] += gi * gq[at[J]];
+        }
+      }
+      const int sw = sym_eig_jacobi(np_, Bm, lam, vt);
+      sweeps[slot] = sw < 0 ? sw : (sweeps[slot] < 0 ? sweeps[slot] : sw);
+      // entry (k, r) of the class: tile r / 16, step k / 4, lane (k % 4, r % 16)
+      auto entry = [&](int k, int r) {
+        return ((size_t)(t + r / 16) * cl.steps + k / 4) * 64 + (k % 4) * 16 + r % 16;
+      };
+      for (int r = 0; r < np_; ++r) {
+        std::fill(v.begin(), v.end(), 0.0);
+        for (int k = 0; k < np_; ++k) v[at[k]] = vt[(size_t)r * np_ + k];
+        w = v;
+        along(C, false, v);   // L z_r
+        along(Ci, true, w);   // L^{-T} z_r
+        for (int k = 0; k < np_; ++k) {
+          const double is = 1.0 / scale(at[k]);
+          A1[entry(k, r)] = v[at[k]] * is;
+          A2[entry(r, k)] = w[at[k]] * is;
+        }
+        L[o + r] = std::max(lam[r], 0.0);  // positive semidefinite form
       }
     }
-    for (int r = 0; r < n; ++r) L[r] = std::max(lam[r], 0.0);  // positive semidefinite form
   };
   // slots t, t + nth, ... per worker; an allocation failure marks the slot (-2) instead of escaping the thread,
   // and workers that cannot be started run on this thread
@@ -371,8 +459,8 @@ void spectral_pointers(const dg_mesh* m, const double** mats, const double** slo
   const size_t n = 3 * (size_t)np * np * np;
   const int ns = spectral_layers(*m, nullptr, nullptr);
   *mats = m->spec;
-  *slots = m->spec + 3 * np * np;
-  *map = reinterpret_cast<const int32_t*>(m->spec + 3 * np * np + (size_t)ns * (2 * n * n + n));
+  *slots = m->spec + np * np;
+  *map = reinterpret_cast<const int32_t*>(m->spec + np * np + (size_t)ns * (2 * block_entries(np) + n));
 }
 
 int launch_spectral_step(const dg_mesh* m, const double* tau_d, const double* u_hat, const double* g, double scale,
@@ -399,14 +487,13 @@ int launch_spectral_step(const dg_mesh* m, const double* tau_d, const double* u_
   A.x = x;
 #define X(p)                                                                                                \
   if (np == p) {                                                                                            \
-    constexpr int nc = spec_nc<p>();                                                                        \
-    const int64_t tiles = (A.ncol + nc - 1) / nc;                                                           \
+    const int64_t tiles = (A.ncol + kTileCols - 1) / kTileCols;                                             \
     const int64_t nb = tiles * nl;                                                                          \
     if (nb > INT32_MAX / 2) return set_error(DG_ERR_ARG, "projection step: mesh too large");                \
     A.tiles = (int)tiles;                                                                                   \
     A.nblocks = (int)nb;                                                                                    \
     const int grid = ((A.nblocks + 7) / 8) * 8;                                                             \
-    hipLaunchKernelGGL((spectral_step_kernel<p, nc>), dim3((unsigned)grid), dim3(kSpecThreads), 0, s, A);   \
+    hipLaunchKernelGGL(spectral_step_kernel<p>, dim3((unsigned)grid), dim3(tile_threads(p)), 0, s, A);      \
     return check_hip(hipGetLastError(), "projection step kernel launch");                                   \
   }
   X(3) X(4) X(5) X(6)
