@@ -20,32 +20,6 @@ namespace dgwm {
 
 namespace {
 
-// N_i(x) of the NP-node Lobatto basis
-template <int NP>
-struct LobattoDen {  // 1 / prod_{j != i} (x_i - x_j)
-  double inv[NP];
-  constexpr LobattoDen() : inv{} {
-    for (int i = 0; i < NP; ++i) {
-      double d = 1.0;
-      for (int j = 0; j < NP; ++j)
-        if (j != i) d *= ct::lobatto<NP>.x[i] - ct::lobatto<NP>.x[j];
-      inv[i] = 1.0 / d;
-    }
-  }
-};
-template <int NP>
-inline constexpr LobattoDen<NP> lobatto_den{};
-
-template <int NP>
-__device__ __forceinline__ double lobatto_basis(int i, double x) {
-  constexpr auto& L = ct::lobatto<NP>;
-  double v = lobatto_den<NP>.inv[i];
-#pragma unroll
-  for (int j = 0; j < NP; ++j)
-    if (j != i) v *= x - L.x[j];
-  return v;
-}
-
 // 1-D prolongation tables P[d][child][l][i] = N_i(xi_c(child, xi_l)) of the
 // coarse cell (identity along directions that are not coarsened).
 template <typename T, int NP>

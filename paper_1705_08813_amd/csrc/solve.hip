@@ -421,6 +421,32 @@ struct Solver {
     }
     return check_hip(hipGetLastError(), "chebyshev");
   }
+  // The coarse end of the V-cycle in one workgroup (kern_mg_tail.hip): first
+  // level that fits, -1 if none does.  Its tables are formed once per solve,
+  // after the eigenvalue estimates, in vectors that the iteration leaves
+  // unused: those of the estimates with an FP32 cycle, the FP32 ones with an
+  // FP64 cycle.
+  char* tail_img = nullptr;
+  int tail_l = -1, tail_threads = 0, tail_groups = 1;
+  template <typename T>
+  bool plan_tail(int deg0, int degc, TailSeg<T>* t) {
+    char* const first = sizeof(T) == 4 ? reinterpret_cast<char*>(d64) : reinterpret_cast<char*>(r32);
+    char* const end = sizeof(T) == 4 ? reinterpret_cast<char*>(dinv + n) : reinterpret_cast<char*>(qq32 + n);
+    tail_l = -1;
+    for (int l = 0; l < nlev && tail_l < 0; ++l)
+      if (mg_tail_segment<T>(m, l, nlev, deg0, degc, kSmoothRange, (size_t)(end - first), t)) tail_l = l;
+    if (tail_l < 0) return false;
+    t->img = tail_img = first;
+    tail_threads = t->threads;
+    tail_groups = t->groups;
+    for (int j = 0; j < t->nlev; ++j) t->lv[j].dinv = dinv_of<T>(tail_l + j);
+    return true;
+  }
+  template <typename T>
+  int make_tail(int deg0, int degc) {
+    TailSeg<T> t;
+    return plan_tail<T>(deg0, degc, &t) ? launch_mg_tail_image<T>(m->np_p, &t, 1, s) : DG_OK;
+  }
   // x = V-cycle(l) b: Chebyshev-Jacobi pre-smoothing, restricted residual,
   // coarse correction, post-smoothing; the coarsest level is solved with the
   // dense pseudo-inverse (or smoothed with a long polynomial).
@@ -433,6 +459,11 @@ struct Solver {
     const double lam = mm->mg[l].lam;
     const dg_prec prec = sizeof(T) == 8 ? DG_F64 : DG_F32;
     int rc;
+    if (l == tail_l) {
+      const TailRun<T> run{tail_img, b, x, tail_threads, tail_groups};
+      if (l == 0) (sizeof(T) == 8 ? applies64 : applies32) += 2 * deg;
+      return launch_mg_tail<T>(m->np_p, &run, 1, s);
+    }
     if (l == L) {
       if (mm->coarse_inv)
         return launch_dense_apply(nn, prec, sizeof(T) == 8 ? (const void*)mm->coarse_inv : (const void*)mm->coarse_inv32,
@@ -639,6 +670,7 @@ int solve_poisson_ws(const dg_mesh* m, const dg_solve_params* sp, const double* 
   const double lmax = 1.1 * mm->lam_max, lmin = mm->lam_max / 30.0;
   const int deg = sp->cheb_degree;
   const int degc = sp->coarse_degree > 0 ? sp->coarse_degree : deg;
+  if (use_mg) DG_TRY(sp->mixed ? S.make_tail<float>(deg, degc) : S.make_tail<double>(deg, degc));
 
   // b' = b - mean(b), ||b'||
   hipLaunchKernelGGL((k_sum<double>), dim3(S.red(S.n)), dim3(kRedThreads), 0, S.s, b, S.n, S.part);
@@ -1309,14 +1341,39 @@ class Batch {
       cur_is_t = !cur_is_t;
     }
   }
+  // tables of the V-cycles' coarse ends (Solver::make_tail), a launch per degree
+  template <typename T>
+  int make_tails(const Set& set) {
+    for (int np = 2; np <= 6; ++np) {
+      std::vector<TailSeg<T>> v;
+      for (BInst* in : set) {
+        TailSeg<T> t;
+        if (in->m->np_p == np && in->S.plan_tail<T>(deg0, degc, &t)) v.push_back(t);
+      }
+      if (int rc = launch_mg_tail_image<T>(np, v.data(), (int)v.size(), s)) return rc;
+    }
+    return DG_OK;
+  }
   template <typename T>
   void vcycle(Prog& P, const Set& set, int l, const std::function<T*(BInst&, int)>& buf) {
     if (set.empty()) return;
     const int deg = l == 0 ? deg0 : degc;
     Set coarse_d, coarse_c, mid;
+    std::vector<std::pair<int, std::vector<TailRun<T>>>> tails;  // by degree
     for (BInst* in : set) {
-      if (l == in->S.nlev - 1) (in->m->coarse_inv ? coarse_d : coarse_c).push_back(in);
+      if (l == in->S.tail_l) {
+        const int np = in->m->np_p;
+        auto g = std::find_if(tails.begin(), tails.end(), [&](const auto& e) { return e.first == np; });
+        if (g == tails.end()) g = tails.insert(tails.end(), {np, {}});
+        g->second.push_back({in->S.tail_img, buf(*in, BB), buf(*in, BX), in->S.tail_threads, in->S.tail_groups});
+        for (int k = 0; l == 0 && k < 2 * deg; ++k) P.count(in, sizeof(T) == 8);
+      } else if (l == in->S.nlev - 1) (in->m->coarse_inv ? coarse_d : coarse_c).push_back(in);
       else mid.push_back(in);
+    }
+    for (const auto& g : tails) {
+      const auto v = g.second;
+      const int np = g.first;
+      P.steps.push_back([v, np](hipStream_t st) { return launch_mg_tail<T>(np, v.data(), (int)v.size(), st); });
     }
     dense<T>(P, coarse_d, l, [&](DenseSeg<T>& g, BInst& in) {
       g.b = buf(in, BB);
@@ -1592,6 +1649,7 @@ int solve_batched(const dg_mesh* const* meshes, int n, const dg_solve_params* sp
     mm->mg[0].lam = mm->lam_max;
     in->applies64 = in->applies32 = 0;  // (the estimates are not part of the solve's count)
   }
+  DG_TRY(B.mixed ? B.make_tails<float>(all) : B.make_tails<double>(all));
   // ||b'|| of every mesh (read back after the eigenvalue estimates)
   {
     Prog pg;
