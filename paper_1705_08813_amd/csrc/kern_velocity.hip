@@ -37,13 +37,23 @@ struct VelShape {
   static constexpr int TRC = 2 * 2 * 8 * FMAX;          // traces [s][side][field][pt]
   static constexpr int FACE0 = NL + LAYO + A1 + TRC;
   static constexpr int FACE = FACE0 > NL + LAYO + A1 + FL + B1 ? FACE0 : NL + LAYO + A1 + FL + B1;
-  // curved cells: 12 trace fields per side and reference-gradient tests
-  static constexpr int A1C = 2 * 2 * 3 * 3 * Q1MAX * NP;
-  static constexpr int FLC = 2 * 12 * FMAX;
-  static constexpr int FACEC = NL + LAYO + A1C + FLC + B1;
+  // curved cells: own layers of all faces, then [t1-swept traces, later 12 flux fields] and [traces, later tests]
+  static constexpr int QS(int q1) { return q1 + 1; }
+  static constexpr int TP(int fp) { return fp + (10 - fp % 8) % 8; }
+  static constexpr int FLP(int fp) { return fp % 32 == 0 ? fp + 8 : fp; }
+  static constexpr int fl_max() {  // faces with normals along x or z, and along y
+    const int a = FLP(NQ * NQY), b = FLP(NQ * NQ);
+    return a > b ? a : b;
+  }
+  static constexpr int A1C0 = 2 * 2 * 3 * 3 * QS(Q1MAX) * NP, FLC = 2 * 12 * fl_max(), A1C = A1C0 > FLC ? A1C0 : FLC;
+  static constexpr int B1C = 2 * 3 * 3 * QS(Q1MAX) * NP, TRC4 = 2 * 2 * 3 * 4 * (FMAX + 7), TBC = TRC4 > B1C ? TRC4 : B1C;
+  static constexpr int FACEC = NL + 3 * LAYO + A1C + TBC;
   static constexpr int VOL = 12 * NPTS;
-  static constexpr int BIG0 = VOL > FACE ? VOL : FACE;
-  static constexpr int BIG = BIG0 > FACEC ? BIG0 : FACEC;
+  template <bool CURVED>
+  static constexpr int big() {
+    const int f = CURVED ? FACEC : FACE;
+    return VOL > f ? VOL : f;
+  }
 };
 
 // Node index of the point at position l along direction D on the line
@@ -814,170 +824,256 @@ __device__ __forceinline__ void vel_faces_dir(const MeshDev& M, const T* s_u, co
   __syncthreads();
 }
 
-// Curved cells: both faces of direction D with general normals.  Traces carry
-// the full reference gradient (12 fields per side), mapped with the stored
-// J^{-1} of each side at the face point; the gradient tests are pulled back
-// to reference derivatives with the own side's J^{-1}.
-template <typename T, int NP, int NQ, int NQY, bool ENR, int D>
-__device__ __forceinline__ void vel_faces_dir_curved(const MeshDev& M, int64_t e, const T* s_u, const T* s_nl,
-                                                     const T* s_nut, T* s_r, T* s_face, const T* s_ut,
-                                                     const T* s_tab, int ex, int ey, int ez, int64_t enr, T rt[3]) {
+// Curved cells: faces with general normals.  Traces carry the full reference
+// gradient (12 fields per side), mapped with the stored J^{-1} of each side at
+// the face point; the gradient tests are pulled back to reference derivatives
+// with the own side's J^{-1}.
+//
+// As on flat cells every 1-D contraction runs on a thread-owned line, so that
+// an LDS read feeds a whole column of a table and the table entries come from
+// scalar registers.  The flux phase has one thread per face point and side; its
+// geometry and psi values are loaded two phases ahead.  48 x 24 x 24 cells, k =
+// 5, FP64: 1,410 us for the cells without enrichment (25,344 of them, 1.8 GB of
+// geometry), 1,556 us with a table read from LDS per product.  What is left is
+// the vector unit at 46% behind 26 barriers with two workgroups a CU; padding
+// the point fields against bank conflicts did not shorten it.
+template <typename T, int NP, int NQ, int NQY, bool ENR>
+struct CurvedFaces {
   using Sh = VelShape<T, NP, NQ, NQY>;
-  constexpr int T1 = D == 0 ? 1 : 0;
-  constexpr int T2 = D == 2 ? 1 : 2;
-  constexpr int Q1 = T1 == 1 ? NQY : NQ;
-  constexpr int Q2 = T2 == 1 ? NQY : NQ;
-  constexpr int FP = Q1 * Q2;
-  constexpr int NP2 = Sh::NP2, NP3 = Sh::NP3;
-  constexpr int QN = Q1 * NP;
-  const int tid = threadIdx.x;
-  constexpr int nt = 256;  // workgroup size of every velocity launch
+  static constexpr int NP2 = Sh::NP2, NP3 = Sh::NP3;
+  static constexpr bool MEM = sizeof(T) == 8;
+  static constexpr TabLayout L = tab_layout(NP, NQ, NQY);
   using TL = FaceTab<NP, NQ, NQY>;
-  const T* S1 = s_tab + (T1 == 1 ? TL::Sy : TL::Sq);
-  const T* Sd1 = s_tab + (T1 == 1 ? TL::Sdy : TL::Sdq);
-  const T* S2 = s_tab + (T2 == 1 ? TL::Sy : TL::Sq);
-  const T* Sd2 = s_tab + (T2 == 1 ? TL::Sdy : TL::Sdq);
-  const T* nd0 = s_tab + TL::nd0;
-  const T* nd1 = s_tab + TL::nd1;
 
-  T* lay = s_face;                 // [s][c][val|d_n][NP2]
-  T* A1 = lay + Sh::LAYO;          // [s][side][c][Sv|Sdv|Sn][q1][i2]
-  T* fl = A1 + Sh::A1C;            // [s][12][pt]
-  T* B1 = fl + Sh::FLC;            // [s][c][value|t1|normal][q1][i2]
+  // Rule along direction d of a face: NQY points along y, NQ along x and z.
+  template <int D>
+  struct Dir {
+    static constexpr int T1 = D == 0 ? 1 : 0, T2 = D == 2 ? 1 : 2;
+    static constexpr int Q1 = T1 == 1 ? NQY : NQ, Q2 = T2 == 1 ? NQY : NQ, FP = Q1 * Q2;
+    // entries between q1 lines, trace fields and flux fields: threads of one instruction work on 8 or fewer neighbouring
+    // points of several fields, which these keep on different LDS banks (18% of the cycles were conflicts without)
+    static constexpr int QS = Sh::QS(Q1), QN = QS * NP, TP = Sh::TP(FP), FL = Sh::FLP(FP);
+    static constexpr int NT = 4 * FP;  // flux threads: (side, point, face)
+    static_assert(NT <= 256, "one flux thread per face point and side");
+  };
 
-  const FaceNb nb0 = face_nb(M, ex, ey, ez, D, 0), nb1 = face_nb(M, ex, ey, ez, D, 1);
-  const bool wall0 = nb0.wall, wall1 = nb1.wall;
+  const MeshDev& M;
+  const int64_t e, enr;
+  const int ex, ey, ez;
+  const T* s_u;
+  const T* s_nl;
+  const T* s_nut;
+  const T* s_ut;
+  const T* s_tab;
+  T* s_r;
+  T* lay;  // own layers [D][s][c][val|d_n][NP2]
+  T* A1;   // t1-swept traces [s][side][c][Sv|Sdv|Sn][i2][q1], then fluxes [s][12][pt]
+  T* TR;   // traces [s][side][c][v|d1|d2|dn][pt], then t2-transposed tests [s][c][3][i2][q1]
+  T geo[10], psi[4];
 
-  for (int t = tid; t < 2 * 3 * NP2; t += nt) {
-    const int s = t / (3 * NP2), rem = t - s * 3 * NP2;
-    const int c = rem / NP2, k = rem - c * NP2;
-    int base, stride;
-    line_of<NP>(D, k % NP, k / NP, base, stride);
-    const T* nd = s ? nd1 : nd0;
-    const T* src = s_u + c * NP3 + base;
-    T der = 0;
-#pragma unroll
-    for (int l = 0; l < NP; ++l) der += nd[l] * src[l * stride];
-    lay[((s * 3 + c) * 2 + 0) * NP2 + k] = src[(s ? NP - 1 : 0) * stride];
-    lay[((s * 3 + c) * 2 + 1) * NP2 + k] = der;
+  // table entries S[q][i], S'[q][i] of the rule along a tangential direction
+  template <int D, int TT>
+  __device__ __forceinline__ T S(int q, int i) const {
+    constexpr int Q = TT == 1 ? NQY : NQ;
+    constexpr auto& tb = ct::tab<NP, Q>;
+    return MEM ? T(M.tab[(TT == 1 && ENR ? L.Sy : L.S) + q * NP + i]) : T(tb.S[q][i]);
   }
-  __syncthreads();
-
-  for (int t = tid; t < 2 * 2 * 3 * 3 * QN; t += nt) {
-    const int q1 = t % Q1;
-    int r = t / Q1;
-    const int i2 = r % NP;
-    r /= NP;
-    const int f = r % 3;
-    r /= 3;
-    const int c = r % 3;
-    r /= 3;
-    const int side = r % 2, s = r / 2;
-    if (side == 1 && (s ? wall1 : wall0)) continue;
-    const T* lv = (side == 0 ? lay + ((s * 3 + c) * 2) * NP2 : s_nl + (((2 * D + s) * 3 + c) * 2) * NP2) +
-                  (f == 2 ? NP2 : 0) + NP * i2;
-    const T* mat = (f == 1 ? Sd1 : S1) + q1 * NP;
-    T acc = 0;
-#pragma unroll
-    for (int i1 = 0; i1 < NP; ++i1) acc += mat[i1] * lv[i1];
-    A1[((((s * 2 + side) * 3 + c) * 3 + f) * Q1 + q1) * NP + i2] = acc;
+  template <int D, int TT>
+  __device__ __forceinline__ T Sd(int q, int i) const {
+    constexpr int Q = TT == 1 ? NQY : NQ;
+    constexpr auto& tb = ct::tab<NP, Q>;
+    return MEM ? T(M.tab[(TT == 1 && ENR ? L.Sdy : L.Sd) + q * NP + i]) : T(tb.Sd[q][i]);
   }
-  __syncthreads();
 
-  const T nu = T(M.nu), theta = T(M.theta);
-  const int nqy_own = ENR ? NQY : NQ;
-  for (int t = tid; t < 2 * FP; t += nt) {
-    const int s = t / FP, pt = t - s * FP;
-    const int q1 = pt % Q1, q2 = pt / Q1;
-    const T sg = s ? T(1) : T(-1);
-    const bool wall = s ? wall1 : wall0;
-    const FaceNb& nb = s ? nb1 : nb0;
-    const int f = 2 * D + s, fn = 2 * D + (1 - s);
-    const double* go = M.geo + (e * M.geo_stride + psi_face_offset(NQ, nqy_own, f) + pt) * 10;
-    T Jo[3][3], Jn[3][3];
+  // own node layers of all six faces: value and d/dxi_D, one line each
+  __device__ __forceinline__ void layers() {
+    constexpr auto& tb = ct::tab<NP, NQ>;  // nd0, nd1 do not depend on the rule
+    for (int t = threadIdx.x; t < 9 * NP2; t += 256) {
+      const int D = t / (3 * NP2), rem = t - D * 3 * NP2, c = rem / NP2, k = rem - c * NP2;
+      int base, stride;
+      line_of<NP>(D, k % NP, k / NP, base, stride);
+      const T* src = s_u + c * NP3 + base;
+      T x[NP], d0 = 0, d1 = 0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+      for (int l = 0; l < NP; ++l) x[l] = src[l * stride];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) Jo[a][d] = T(go[3 * a + d]);
-    const T wf = T(go[9]);
-    T um[3], up[3], gm[3][3], gp[3][3];
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      if (side == 1 && wall) continue;
-      if (side == 1) {
-        const int nqy_nb = nb.enr_nb >= 0 ? M.nq_wn : NQ;  // the neighbour's own point layout
-        const double* gn = M.geo + (nb.enb * M.geo_stride + psi_face_offset(NQ, nqy_nb, fn) + pt) * 10;
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-          for (int d = 0; d < 3; ++d) Jn[a][d] = T(gn[3 * a + d]);
+      for (int l = 0; l < NP; ++l) {
+        d0 += T(tb.nd0[l]) * x[l];
+        d1 += T(tb.nd1[l]) * x[l];
       }
+      T* o = lay + ((D * 6 + c) * 2) * NP2 + k;
+      o[0] = x[0];
+      o[NP2] = d0;
+      o[6 * NP2] = x[NP - 1];
+      o[7 * NP2] = d1;
+    }
+  }
+
+  // geometry (J^{-1}, weight) and psi of the thread's point and side; a wall has no other side: its thread reads the own
+  // one
+  template <int D>
+  __device__ __forceinline__ void fetch() {
+    using DD = Dir<D>;
+    const int t = threadIdx.x;
+    if (t >= DD::NT) return;
+    const int s = t / (2 * DD::FP), r = t - s * 2 * DD::FP, side = r & 1, pt = r >> 1;
+    const FaceNb nb = face_nb(M, ex, ey, ez, D, s);
+    const bool other = side && !nb.wall;
+    const int f = 2 * D + (other ? 1 - s : s);
+    const bool en = other ? nb.enr_nb >= 0 : ENR;  // the cell has the wall-normal rule and psi
+    const int64_t cell = other ? nb.enb : e;
+    const double* g = M.geo + (cell * M.geo_stride + psi_face_offset(NQ, other ? (en ? M.nq_wn : NQ) : (ENR ? NQY : NQ), f) + pt) * 10;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const T* a = A1 + (((s * 2 + side) * 3 + c) * 3) * QN + q1 * NP;
-        T v = 0, d1 = 0, d2 = 0, dn = 0;
+    for (int j = 0; j < 10; ++j) geo[j] = T(g[j]);
 #pragma unroll
-        for (int i2 = 0; i2 < NP; ++i2) {
-          const T b2 = S2[q2 * NP + i2], bd2 = Sd2[q2 * NP + i2];
-          v += b2 * a[i2];
-          d1 += b2 * a[QN + i2];
-          d2 += bd2 * a[i2];
-          dn += b2 * a[2 * QN + i2];
+    for (int j = 0; j < 4; ++j) psi[j] = 0;
+    if (en) {
+      const double* ps = M.psi + ((size_t)(other ? nb.enr_nb : enr) * M.psi_pts + M.psi_off[1 + f] + pt) * 4;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) psi[j] = T(ps[j]);
+    }
+  }
+
+  // t1 sweeps of both sides' layers (threads from the high end: the phase is shared with add<D - 1>)
+  template <int D>
+  __device__ __forceinline__ void traces() {
+    using DD = Dir<D>;
+    const bool wall0 = face_nb(M, ex, ey, ez, D, 0).wall, wall1 = face_nb(M, ex, ey, ez, D, 1).wall;
+    for (int t = 255 - (int)threadIdx.x; t < 24 * NP; t += 256) {
+      const int i2 = t % NP;
+      int r = t / NP;
+      const int c = r % 3;
+      r /= 3;
+      const int side = r & 1, s = (r >> 1) & 1, dn = r >> 2;
+      if (side && (s ? wall1 : wall0)) continue;
+      const T* lv = (side ? s_nl + (((2 * D + s) * 3 + c) * 2 + dn) * NP2 : lay + (((D * 2 + s) * 3 + c) * 2 + dn) * NP2) +
+                    NP * i2;
+      T x[NP];
+#pragma unroll
+      for (int i = 0; i < NP; ++i) x[i] = lv[i];
+      T* o = A1 + (((s * 2 + side) * 3 + c) * 3 + (dn ? 2 : 0)) * DD::QN + i2 * DD::QS;
+#pragma unroll
+      for (int q = 0; q < DD::Q1; ++q) {
+        T v = 0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) v += S<D, DD::T1>(q, i) * x[i];
+        o[q] = v;
+      }
+      if (!dn) {
+#pragma unroll
+        for (int q = 0; q < DD::Q1; ++q) {
+          T v = 0;
+#pragma unroll
+          for (int i = 0; i < NP; ++i) v += Sd<D, DD::T1>(q, i) * x[i];
+          o[DD::QN + q] = v;
         }
-        T gr[3];
-        gr[T1] = d1;
-        gr[T2] = d2;
-        gr[D] = dn;
-        T* uo = side == 0 ? um : up;
-        T(*go3)[3] = side == 0 ? gm : gp;
-        uo[c] = v;
+      }
+    }
+  }
+
+  // t2 sweeps: value and three reference derivatives at the points
+  template <int D>
+  __device__ __forceinline__ void fields() {
+    using DD = Dir<D>;
+    for (int t = threadIdx.x; t < 24 * DD::Q1; t += 256) {
+      const int q1 = t % DD::Q1;
+      int r = t / DD::Q1;
+      const int c = r % 3;
+      r /= 3;
+      const int side = r & 1, s = (r >> 1) & 1, h = r >> 2;
+      const T* a = A1 + (((s * 2 + side) * 3 + c) * 3) * DD::QN + q1;
+      T* o = TR + (((s * 2 + side) * 3 + c) * 4) * DD::TP + q1;
+      T x[NP];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const T(*Jx)[3] = side == 0 ? Jo : Jn;
-          go3[c][d] = gr[0] * Jx[0][d] + gr[1] * Jx[1][d] + gr[2] * Jx[2][d];
+      for (int i = 0; i < NP; ++i) x[i] = a[(h ? DD::QN : 0) + i * DD::QS];
+#pragma unroll
+      for (int q = 0; q < DD::Q2; ++q) {
+        T v = 0;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) v += S<D, DD::T2>(q, i) * x[i];
+        o[(h ? DD::TP : 0) + DD::Q1 * q] = v;
+      }
+      if (!h) {
+#pragma unroll
+        for (int q = 0; q < DD::Q2; ++q) {
+          T v = 0;
+#pragma unroll
+          for (int i = 0; i < NP; ++i) v += Sd<D, DD::T2>(q, i) * x[i];
+          o[2 * DD::TP + DD::Q1 * q] = v;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) x[i] = a[2 * DD::QN + i * DD::QS];
+#pragma unroll
+        for (int q = 0; q < DD::Q2; ++q) {
+          T v = 0;
+#pragma unroll
+          for (int i = 0; i < NP; ++i) v += S<D, DD::T2>(q, i) * x[i];
+          o[3 * DD::TP + DD::Q1 * q] = v;
         }
       }
     }
-    T psim = 0, gpsim[3] = {0, 0, 0};
-    if (ENR) {
-      const double* ps = M.psi + ((size_t)enr * M.psi_pts + M.psi_off[1 + f] + pt) * 4;
-      psim = T(ps[0]);
-      gpsim[0] = T(ps[1]);
-      gpsim[1] = T(ps[2]);
-      gpsim[2] = T(ps[3]);
+  }
+
+  // fluxes: the two threads of a point form their side's velocity and stress, exchange them, and write the value part
+  // (other side's thread) and the gradient part (own side's)
+  template <int D>
+  __device__ __forceinline__ void flux(T rt[3]) {
+    using DD = Dir<D>;
+    constexpr int FP = DD::FP;
+    const int t = threadIdx.x;
+    if (t >= DD::NT) return;
+    const int s = t / (2 * DD::FP), r = t - s * 2 * FP, side = r & 1, pt = r >> 1;
+    const FaceNb nb = face_nb(M, ex, ey, ez, D, s);
+    const int f = 2 * D + s;
+    const T nu = T(M.nu), theta = T(M.theta), tau = T(M.tauF[e * 6 + f]);
+    T u[3], g[3][3];
+    const T* a = TR + ((s * 2 + side) * 3 * 4) * DD::TP + pt;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      T gr[3];
+      u[c] = a[(c * 4) * DD::TP];
+      gr[DD::T1] = a[(c * 4 + 1) * DD::TP];
+      gr[DD::T2] = a[(c * 4 + 2) * DD::TP];
+      gr[D] = a[(c * 4 + 3) * DD::TP];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) g[c][d] = gr[0] * geo[d] + gr[1] * geo[3 + d] + gr[2] * geo[6 + d];
+    }
+    const T* ut = side ? s_nut + f * 3 : s_ut;
+    if (ENR || nb.enr_nb >= 0) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        um[c] += psim * s_ut[c];
+        const T uc = (side ? nb.enr_nb >= 0 : ENR) ? ut[c] : T(0);
+        u[c] += psi[0] * uc;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) gm[c][k] += s_ut[c] * gpsim[k];
+        for (int k = 0; k < 3; ++k) g[c][k] += uc * psi[1 + k];
       }
     }
-    if (wall) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        up[c] = -um[c];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) gp[c][k] = gm[c][k];
-      }
-    } else if (nb.enr_nb >= 0) {
-      const double* ps = M.psi + ((size_t)nb.enr_nb * M.psi_pts + M.psi_off[1 + fn] + pt) * 4;
-      const T psip = T(ps[0]);
-      const T gpp[3] = {T(ps[1]), T(ps[2]), T(ps[3])};
-      const T* ut = s_nut + f * 3;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        up[c] += psip * ut[c];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) gp[c][k] += ut[c] * gpp[k];
-      }
-    }
-    T nv[3];
+    // the own side's outward normal and weight
+    T nv[3], wf;
     {
-      const T nr = sqrt(Jo[D][0] * Jo[D][0] + Jo[D][1] * Jo[D][1] + Jo[D][2] * Jo[D][2]);
+      const T x = geo[3 * D], y = geo[3 * D + 1], z = geo[3 * D + 2];
+      const T q = (s ? T(1) : T(-1)) / sqrt(x * x + y * y + z * z);
+      const T n[3] = {q * x, q * y, q * z};
 #pragma unroll
-      for (int d = 0; d < 3; ++d) nv[d] = sg * Jo[D][d] / nr;
+      for (int d = 0; d < 3; ++d) {
+        const T o = pair_swap(n[d]);
+        nv[d] = side ? o : n[d];
+      }
+      const T o = pair_swap(geo[9]);
+      wf = side ? o : geo[9];
     }
-    const T tau = T(M.tauF[e * 6 + f]);
+    T um[3], up[3], vs[3];  // vs: 2 eps(u) n of both sides added
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      T w = 0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) w += (g[c][k] + g[k][c]) * nv[k];
+      const T uo = pair_swap(u[c]), wo = pair_swap(w);
+      um[c] = side ? uo : u[c];
+      up[c] = nb.wall ? -um[c] : (side ? u[c] : uo);
+      vs[c] = nb.wall ? T(2) * (side ? wo : w) : w + wo;
+    }
     const T unm = um[0] * nv[0] + um[1] * nv[1] + um[2] * nv[2];
     const T unp = up[0] * nv[0] + up[1] * nv[1] + up[2] * nv[2];
     const T am = unm < 0 ? -unm : unm, ap = unp < 0 ? -unp : unp;
@@ -985,80 +1081,125 @@ __device__ __forceinline__ void vel_faces_dir_curved(const MeshDev& M, int64_t e
     T jmp[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) jmp[c] = um[c] - up[c];
-    T* fo = fl + s * 12 * FP + pt;
+    T* fo = A1 + s * 12 * DD::FL + pt;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      T visc = 0;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) visc += (gm[c][k] + gm[k][c] + gp[c][k] + gp[k][c]) * nv[k];
-      const T fv = T(0.5) * (um[c] * unm + up[c] * unp) + T(0.5) * lam * jmp[c] - T(0.5) * nu * visc +
+      const T fv = T(0.5) * (um[c] * unm + up[c] * unp) + T(0.5) * lam * jmp[c] - T(0.5) * nu * vs[c] +
                    tau * nu * jmp[c];
-      T F[3];
+      if (side) {
+        fo[c * DD::FL] = wf * fv;
+      } else {
+        T F[3], Fr[3];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) F[k] = -theta * nu * T(0.5) * (jmp[c] * nv[k] + jmp[k] * nv[c]);
-      T Fr[3];
+        for (int k = 0; k < 3; ++k) F[k] = -theta * nu * T(0.5) * (jmp[c] * nv[k] + jmp[k] * nv[c]);
 #pragma unroll
-      for (int a = 0; a < 3; ++a) Fr[a] = F[0] * Jo[a][0] + F[1] * Jo[a][1] + F[2] * Jo[a][2];
-      fo[c * FP] = wf * fv;
-      fo[(3 + c) * FP] = wf * Fr[T1];
-      fo[(6 + c) * FP] = wf * Fr[T2];
-      fo[(9 + c) * FP] = wf * Fr[D];
-      if (ENR) rt[c] += wf * (psim * fv + F[0] * gpsim[0] + F[1] * gpsim[1] + F[2] * gpsim[2]);
-    }
-  }
-  __syncthreads();
-
-  for (int t = tid; t < 2 * 3 * QN; t += nt) {
-    const int i2 = t % NP;
-    int r = t / NP;
-    const int q1 = r % Q1;
-    r /= Q1;
-    const int c = r % 3, s = r / 3;
-    const T* fo = fl + s * 12 * FP + q1;
-    T a0 = 0, a1 = 0, a3 = 0;
-#pragma unroll
-    for (int q2 = 0; q2 < Q2; ++q2) {
-      const T b2 = S2[q2 * NP + i2], bd2 = Sd2[q2 * NP + i2];
-      a0 += b2 * fo[c * FP + Q1 * q2] + bd2 * fo[(6 + c) * FP + Q1 * q2];
-      a1 += b2 * fo[(3 + c) * FP + Q1 * q2];
-      a3 += b2 * fo[(9 + c) * FP + Q1 * q2];
-    }
-    T* o = B1 + ((s * 3 + c) * 3) * QN + q1 * NP + i2;
-    o[0] = a0;
-    o[QN] = a1;
-    o[2 * QN] = a3;
-  }
-  __syncthreads();
-
-  for (int t = tid; t < 3 * NP2; t += nt) {
-    const int c = t / NP2, k = t - c * NP2;
-    const int i1 = k % NP, i2 = k / NP;
-    T rv[2], bn[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const T* b = B1 + ((s * 3 + c) * 3) * QN + i2;
-      T v = 0, n = 0;
-#pragma unroll
-      for (int q1 = 0; q1 < Q1; ++q1) {
-        v += S1[q1 * NP + i1] * b[q1 * NP] + Sd1[q1 * NP + i1] * b[QN + q1 * NP];
-        n += S1[q1 * NP + i1] * b[2 * QN + q1 * NP];
+        for (int x = 0; x < 3; ++x) Fr[x] = F[0] * geo[3 * x] + F[1] * geo[3 * x + 1] + F[2] * geo[3 * x + 2];
+        fo[(3 + c) * DD::FL] = wf * Fr[DD::T1];
+        fo[(6 + c) * DD::FL] = wf * Fr[DD::T2];
+        fo[(9 + c) * DD::FL] = wf * Fr[D];
+        if (ENR) rt[c] += wf * (psi[0] * fv + F[0] * psi[1] + F[1] * psi[2] + F[2] * psi[3]);
       }
-      rv[s] = v;
-      bn[s] = n;
     }
+  }
+
+  // t2-transposed tests: value with the T2 derivative, T1 derivative, normal derivative
+  template <int D>
+  __device__ __forceinline__ void tests() {
+    using DD = Dir<D>;
+    constexpr int FL = DD::FL, Q1 = DD::Q1, Q2 = DD::Q2;
+    for (int t = threadIdx.x; t < 18 * Q1; t += 256) {
+      const int q1 = t % Q1;
+      int r = t / Q1;
+      const int c = r % 3;
+      r /= 3;
+      const int s = r & 1, kind = r >> 1;
+      const T* fo = A1 + (s * 12 + (kind == 0 ? c : (kind == 1 ? 3 + c : 9 + c))) * FL + q1;
+      T x[Q2], o[NP];
+#pragma unroll
+      for (int q = 0; q < Q2; ++q) x[q] = fo[Q1 * q];
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        o[i] = 0;
+#pragma unroll
+        for (int q = 0; q < Q2; ++q) o[i] += S<D, DD::T2>(q, i) * x[q];
+      }
+      if (kind == 0) {
+#pragma unroll
+        for (int q = 0; q < Q2; ++q) x[q] = fo[6 * FL + Q1 * q];
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+          for (int q = 0; q < Q2; ++q) o[i] += Sd<D, DD::T2>(q, i) * x[q];
+      }
+      T* b = TR + ((s * 3 + c) * 3 + kind) * DD::QN + q1;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) b[i * DD::QS] = o[i];
+    }
+  }
+
+  // t1-transposed tests, spread onto the lines of nodes along D: a pair of threads per line, one face each
+  template <int D>
+  __device__ __forceinline__ void add() {
+    using DD = Dir<D>;
+    constexpr int Q1 = DD::Q1;
+    const T* S1 = s_tab + (DD::T1 == 1 ? TL::Sy : TL::Sq);
+    const T* Sd1 = s_tab + (DD::T1 == 1 ? TL::Sdy : TL::Sdq);
+    static_assert(6 * NP2 <= 256, "one pass");
+    const int t = threadIdx.x;
+    if (t >= 6 * NP2) return;
+    const int s = t & 1, c = (t >> 1) / NP2, k = (t >> 1) - c * NP2, i1 = k % NP, i2 = k / NP;
+    const T* b = TR + ((s * 3 + c) * 3) * DD::QN + i2 * DD::QS;
+    T v = 0, n = 0;
+#pragma unroll
+    for (int q = 0; q < Q1; ++q) {
+      const T w = S1[q * NP + i1];
+      v += w * b[q] + Sd1[q * NP + i1] * b[DD::QN + q];
+      n += w * b[2 * DD::QN + q];
+    }
+    const T no = pair_swap(n), n0 = s ? no : n, n1 = s ? n : no;
     int base, stride;
     line_of<NP>(D, i1, i2, base, stride);
     T* dst = s_r + c * NP3 + base;
+    // thread s takes its own face's half of the line: the value test falls on its end node
 #pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T add = nd0[l] * bn[0] + nd1[l] * bn[1];
-      if (l == 0) add += rv[0];
-      if (l == NP - 1) add += rv[1];
-      dst[l * stride] += add;
+    for (int j = 0; j < (NP + 1) / 2; ++j) {
+      const int l = s ? NP - 1 - j : j;
+      if (s && l < (NP + 1) / 2) continue;  // (the middle node of an odd count is thread 0's)
+      dst[l * stride] += s_tab[TL::nd0 + l] * n0 + s_tab[TL::nd1 + l] * n1 + (j == 0 ? v : T(0));
     }
   }
-  __syncthreads();
-}
+
+  template <int D>
+  __device__ __forceinline__ void middle(T rt[3]) {
+    fields<D>();
+    __syncthreads();
+    flux<D>(rt);
+    __syncthreads();
+    tests<D>();
+    __syncthreads();
+  }
+
+  __device__ __forceinline__ void run(T rt[3]) {
+    layers();
+    fetch<0>();
+    __syncthreads();
+    traces<0>();
+    __syncthreads();
+    middle<0>(rt);
+    fetch<1>();
+    add<0>();
+    traces<1>();
+    __syncthreads();
+    middle<1>(rt);
+    fetch<2>();
+    add<1>();
+    traces<2>();
+    __syncthreads();
+    middle<2>(rt);
+    add<2>();
+    __syncthreads();
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Affine (box) cells: face terms folded into the volume quadrature.
@@ -1564,7 +1705,7 @@ __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __re
   constexpr int NP3 = Sh::NP3, NPTS = Sh::NPTS;
   __shared__ T s_u[3 * NP3];
   __shared__ T s_r[3 * NP3];
-  __shared__ T s_big[Sh::BIG];
+  __shared__ T s_big[Sh::template big<CURVED>()];
   __shared__ T s_ut[3 * LE];      // enrichment coefficients [c][B]
   __shared__ T s_nut[18 * LE];    // the neighbours' ones [face][c][B]
   __shared__ T s_red[3 * LE * 4];
@@ -1628,7 +1769,18 @@ __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __re
       }
     }
   }
-  if (CURVED) load_face_tab<T, NP, NQ, NQY, ENR>(tab, s_tab);
+  // curved cells: J^{-1} and weight as well, most of what the kernel reads
+  T gfv[CURVED ? NPASS : 1][10];
+  if constexpr (CURVED) {
+#pragma unroll
+    for (int kp = 0; kp < NPASS; ++kp) {
+      const int pt = tid + kp * nt;
+      const double* g = M.geo + (e * M.geo_stride + (pt < NPTS ? pt : 0)) * 10;
+#pragma unroll
+      for (int j = 0; j < 10; ++j) gfv[kp][j] = T(g[j]);
+    }
+    load_face_tab<T, NP, NQ, NQY, ENR>(tab, s_tab);
+  }
   __syncthreads();
 
   T* s_val = s_big;             // [c][pt]
@@ -1668,12 +1820,11 @@ __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __re
     const int qx = pt % NQ, qy = (pt / NQ) % NQY, qz = pt / (NQ * NQY);
     T wq, Ji[3][3];
     if (CURVED) {
-      const double* g = M.geo + (e * M.geo_stride + pt) * 10;
 #pragma unroll
       for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int d = 0; d < 3; ++d) Ji[a][d] = T(g[3 * a + d]);
-      wq = T(g[9]);
+        for (int d = 0; d < 3; ++d) Ji[a][d] = gfv[CURVED ? kp : 0][3 * a + d];
+      wq = gfv[CURVED ? kp : 0][9];
     } else {
       wq = T(tbx.w[qx]) * T(tby.w[qy]) * T(tbx.w[qz]) * vol;
     }
@@ -1796,6 +1947,12 @@ __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __re
   }
   __syncthreads();
 
+  T* const s_nl = s_big;
+  T* const s_face = s_big + Sh::NL;
+  CurvedFaces<T, NP, NQ, NQY, ENR> F{M,    e,     enr, ex,     ey,                  ez,     s_u,
+                                     s_nl, s_nut, s_ut, s_tab, s_r, s_face, s_face + 3 * Sh::LAYO,
+                                     s_face + 3 * Sh::LAYO + Sh::A1C};
+
   // integrate: W = sum_d D_d^T G_d / h_d, then transposed interpolation.
   // The x and y parts are formed in place (one phase); each z line then adds
   // its own D_z^T G_z to them and applies S_z^T directly.
@@ -1840,32 +1997,22 @@ __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __re
   }
 
   // faces: neighbour layers of all six faces (one phase), then each direction
-  T* s_nl = s_big;
-  T* s_face = s_big + Sh::NL;
   {
     // neighbours across y = 0 and y = 1 (wrapped; unused on walls)
     const int y0 = ey == 0 ? M.ny - 1 : ey - 1, y1 = ey + 1 == M.ny ? 0 : ey + 1;
     nb_store<T, NP, NQ, CURVED, LE>(M, nbl, s_nl, s_nut, ex, ey, ez, ix, iz, T(M.ihy[y0]), T(M.ihy[y1]));
   }
   __syncthreads();
-  if (CURVED)
-    vel_faces_dir_curved<T, NP, NQ, NQY, ENR, 0>(M, e, s_u, s_nl, s_nut, s_r, s_face, s_ut, s_tab, ex, ey, ez, enr,
-                                                 rt);
-  else
-    vel_faces_dir<T, NP, NQ, NQY, ENR, 0, MS, LE>(M, s_u, s_nl, s_nut, s_r, s_face, s_ut, ex, ey, ez, enr, hx, hy, hz, ix, iy,
-                                           iz, rt);
-  if (CURVED)
-    vel_faces_dir_curved<T, NP, NQ, NQY, ENR, 1>(M, e, s_u, s_nl, s_nut, s_r, s_face, s_ut, s_tab, ex, ey, ez, enr,
-                                                 rt);
-  else
-    vel_faces_dir<T, NP, NQ, NQY, ENR, 1, MS, LE>(M, s_u, s_nl, s_nut, s_r, s_face, s_ut, ex, ey, ez, enr, hx, hy, hz, ix, iy,
-                                           iz, rt);
-  if (CURVED)
-    vel_faces_dir_curved<T, NP, NQ, NQY, ENR, 2>(M, e, s_u, s_nl, s_nut, s_r, s_face, s_ut, s_tab, ex, ey, ez, enr,
-                                                 rt);
-  else
-    vel_faces_dir<T, NP, NQ, NQY, ENR, 2, MS, LE>(M, s_u, s_nl, s_nut, s_r, s_face, s_ut, ex, ey, ez, enr, hx, hy, hz, ix, iy,
-                                           iz, rt);
+  if constexpr (CURVED) {
+    F.run(rt);
+  } else {
+    vel_faces_dir<T, NP, NQ, NQY, ENR, 0, MS, LE>(M, s_u, s_nl, s_nut, s_r, s_face, s_ut, ex, ey, ez, enr, hx, hy, hz,
+                                                  ix, iy, iz, rt);
+    vel_faces_dir<T, NP, NQ, NQY, ENR, 1, MS, LE>(M, s_u, s_nl, s_nut, s_r, s_face, s_ut, ex, ey, ez, enr, hx, hy, hz,
+                                                  ix, iy, iz, rt);
+    vel_faces_dir<T, NP, NQ, NQY, ENR, 2, MS, LE>(M, s_u, s_nl, s_nut, s_r, s_face, s_ut, ex, ey, ez, enr, hx, hy, hz,
+                                                  ix, iy, iz, rt);
+  }
 
   for (int i = tid; i < 3 * NP3; i += nt) r[e * 3 * NP3 + i] = s_r[i];
   if constexpr (ENR && LE == 1) {
