@@ -42,7 +42,7 @@ BYTES_PER_DOF_F64 = 16.0
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for name in ("kern_velocity.hip", "kern_common.h", "kern_poisson.hip"):
+    for name in ("kern_velocity.hip", "kern_residual.hip", "kern_common.h", "kern_poisson.hip"):
         with open(os.path.join(ROOT, "paper_1705_08813_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -51,10 +51,11 @@ struct Ends {
 // turn (3 (k+1)^2 threads a cell).  Every value is read and written by whole
 // lines, coefficients come as wide scalar loads from the mesh's tables.
 // MINV leaves out |J| M M M: the result is M^{-1} V u.
-// On the 64 x 32 x 32 mesh, k = 4 (57,344 such cells): 215 us with M^{-1}, where
-// the quadrature kernel took 1145 us and the inverse mass another 72 us; about
-// 70 FMAs per unknown, so what bounds it are the seven reads of u (own cell and
-// six neighbours, mostly from L2) and the barriers between the six phases.
+// On the 64 x 32 x 32 mesh, k = 4 (61,440 such cells, next to the walls' layers
+// too): 239 us with M^{-1}, where the quadrature kernel took 1,145 us and the
+// inverse mass another 72 us; about 70 FMAs per unknown, so what bounds it are
+// the seven reads of u (own cell and six neighbours, mostly from L2) and the
+// barriers between the six phases.
 template <typename T, int NP, int NQ, bool MINV>
 __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T theta, const T* __restrict__ u,
                                               T* __restrict__ r, int first, int ncells, int layer_lo, int nlayers) {

@@ -9,6 +9,11 @@
 // Viscous terms: linear with constant nu, so they separate exactly into 1-D
 // operators (see viscous_cells in kern_linear.hip for the form); only an
 // enriched neighbour's psi u~ enters by quadrature.
+//
+// 64 x 32 x 32 mesh, k = 4, 61,440 cells: 700 us in FP64 and 390 us in FP32, where
+// the collocation-gradient kernel took 1,224 us and 770 us.  It is bound by the
+// vector unit (some 5,000 instructions a cell, 72% busy) and the eight
+// barriers of a cell; memory would allow 110 us (0.55 GB).
 #include "batch.h"
 #include "velocity.h"
 

@@ -2025,7 +2025,7 @@ __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __re
   }
 }
 
-// FP32 affine cells take the folded-face path (vel_cell below).
+// FP32 enriched cells of flat meshes take the folded-face path (vel_cell below).
 template <typename T>
 __host__ __device__ constexpr bool vel_use_affine() { return sizeof(T) == 4; }
 
@@ -2043,12 +2043,14 @@ __host__ __device__ constexpr int vel_wg_per_cu() {
   return by_lds < by_regs ? by_lds : by_regs;
 }
 
-// FP32 affine cells take the folded-face path (814 us against 1009 us for
-// the general one on the 64x32x32 k = 4 mesh).  In FP64 that path reads one
-// 8-byte LDS value per FMA in its extrapolations and lost to the general
-// path's line-owned face phases (1516 us against 1430 us), so FP64, curved
-// cells and the largest degrees take the general path.
-// (degree-1 enrichment weights, LE = 8, always take the general path)
+// Cells that kern_residual.hip does not take: enriched cells, curved cells and,
+// with degree-1 weights, the cells next to an enriched layer.  FP32 enriched
+// cells of flat meshes run the folded-face path (measured on all cells of the
+// 64 x 32 x 32 mesh, k = 4: 814 us against 1,009 us for the general one).  In FP64
+// that path reads one 8-byte LDS value per FMA in its extrapolations and lost
+// to the general path's line-owned face phases (1,516 us against 1,430 us), so
+// FP64, curved cells, degree-1 weights and the largest degrees take the general
+// path.  The 4,096 enriched cells of that mesh: 85 us in FP32, 155 us in FP64.
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, int LE = 1>
 __device__ __forceinline__ void vel_cell(const MeshDev& M, const T* __restrict__ u, T* __restrict__ r, int b,
                                          int layer_lo, int nlayers, int layer_step = 1) {
