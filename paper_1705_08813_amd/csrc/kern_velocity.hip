@@ -2035,7 +2035,7 @@ __host__ __device__ constexpr bool vel_use_affine() { return sizeof(T) == 4; }
 // cells 128: below that they spill.)
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, int LE = 1>
 __host__ __device__ constexpr int vel_wg_per_cu() {
-  if (CURVED) return 2;
+  if (CURVED) return sizeof(T) == 8 ? 2 : 4;  // FP32, k = 5: 0.90 ms with room for four, 1.05 ms for two
   if (LE != 1) return ENR ? 2 : 3;  // general path; enriched cells hold 24 test-row sums
   if (!vel_use_affine<T>() || !AffShape<T, NP, NQ, NQY>::fits) return 3;
   const int by_lds = (160 * 1024) / AffShape<T, NP, NQ, NQY>::BYTES;
