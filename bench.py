@@ -167,7 +167,7 @@ def main():
     traffic = load_traffic(n_vel)
     roofline = {"bound": "alu", "achieved": round(ach_tflops, 3), "peak": FP64_VEC_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(ach_tflops / FP64_VEC_TFLOPS, 4), "traffic": traffic,
-                "kernel": "velocity residual (vel_kernel regular + enriched launches), FP64",
+                "kernel": "velocity residual (residual_kernel and enriched vel_kernel launches), FP64",
                 "per_launch_ms": round(t_vel * 1e3, 4), "algorithmic_flop_per_dof": VEL_FLOP_PER_DOF}
     out = {"metric": METRIC, "value": value, "unit": "DoFs/s", "n_gpus": 1, "steps": K, "warmup": args.warmup,
            "ms_per_step": wall / K * 1e3, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
