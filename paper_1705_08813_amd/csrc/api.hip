@@ -303,8 +303,8 @@ int dg_setup_mesh(const dg_mesh_params* params, const double* tau_w_host, void* 
   for (int q = 0; q < P.nq_wn; ++q) tu[Lu.size + P.nq_u + q] = tu[Lu.gy + q];
   fill_lin_ops(m->np_u, tu.data() + lin_offset(m->np_u, P.nq_u, P.nq_wn));
   fill_projection(m->np_u, P.nq_u, tu.data() + proj_offset(m->np_u, P.nq_u, P.nq_wn));
-  for (int i = 0; i < m->np_u * P.nq_u; ++i)
-    reinterpret_cast<float*>(tu.data() + s32_offset(m->np_u, P.nq_u, P.nq_wn))[i] = (float)tu[Lu.S + i];
+  for (int i = 0; i < Lu.size; ++i)
+    reinterpret_cast<float*>(tu.data() + s32_offset(m->np_u, P.nq_u, P.nq_wn))[i] = (float)tu[i];
   fill_mix_ops(m->np_u, m->np_p, tu.data() + mix_offset(m->np_u, P.nq_u, P.nq_wn));
   fill_tables(m->np_p, P.nq_p, P.nq_p, tp.data());
   fill_poisson_ops(m->np_p, P.nq_p, tp.data() + tab_layout(m->np_p, P.nq_p, P.nq_p).size);

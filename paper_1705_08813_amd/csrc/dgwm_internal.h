@@ -107,7 +107,7 @@ __host__ __device__ constexpr int lin_offset(int np, int nq, int nqy) { return t
 // face acts on every polynomial test function like the nodal field Pi x Pi.
 __host__ __device__ constexpr int proj_offset(int np, int nq, int nqy) { return lin_offset(np, nq, nqy) + lin_ops(np).size; }
 
-// Behind that: S[q][i] = N_i(g_q) in float (FP32 kernels).
+// Behind that: the tables of tab_layout in float (FP32 kernels).
 __host__ __device__ constexpr int s32_offset(int np, int nq, int nqy) { return proj_offset(np, nq, nqy) + np * nq; }
 
 // 1-D operators between the velocity basis N (npu nodes) and the pressure
@@ -119,7 +119,7 @@ struct MixOps {
   int Mup, Gu, Gp, size;
 };
 __host__ __device__ constexpr MixOps mix_ops(int npu, int npp) { return MixOps{0, npu * npp, 2 * npu * npp, 3 * npu * npp}; }
-__host__ __device__ constexpr int mix_offset(int np, int nq, int nqy) { return s32_offset(np, nq, nqy) + (np * nq + 1) / 2; }
+__host__ __device__ constexpr int mix_offset(int np, int nq, int nqy) { return s32_offset(np, nq, nqy) + (tab_layout(np, nq, nqy).size + 1) / 2; }
 
 // Points of the enrichment tables of one enriched cell: the volume rule
 // nq x nqy x nq, then the six faces f = 2d + s in order.  Face (d,s) has

@@ -841,7 +841,6 @@ template <typename T, int NP, int NQ, int NQY, bool ENR>
 struct CurvedFaces {
   using Sh = VelShape<T, NP, NQ, NQY>;
   static constexpr int NP2 = Sh::NP2, NP3 = Sh::NP3;
-  static constexpr bool MEM = sizeof(T) == 8;
   static constexpr TabLayout L = tab_layout(NP, NQ, NQY);
   using TL = FaceTab<NP, NQ, NQY>;
 
@@ -871,19 +870,18 @@ struct CurvedFaces {
   T* TR;   // traces [s][side][c][v|d1|d2|dn][pt], then t2-transposed tests [s][c][3][i2][q1]
   T geo[10], psi[4];
 
-  // table entries S[q][i], S'[q][i] of the rule along a tangential direction
-  template <int D, int TT>
-  __device__ __forceinline__ T S(int q, int i) const {
-    constexpr int Q = TT == 1 ? NQY : NQ;
-    constexpr auto& tb = ct::tab<NP, Q>;
-    return MEM ? T(M.tab[(TT == 1 && ENR ? L.Sy : L.S) + q * NP + i]) : T(tb.S[q][i]);
+  // The 1-D tables in the kernel's precision, taken anew in every phase (see const_tab).  In FP32 a compile-time table
+  // puts a literal into every FMA, 40 KB of code and 128 registers with spills at k = 5 (82 here): a mesh that gives a
+  // CU few cells waits for that code.  FP32 residual, k = 5: 8 x 4 x 4 cells 51.5 -> 44.4 us, 48 x 24 x 24 cells
+  // 896 -> 781 us; k = 3, 8 x 4 x 4 cells 32.5 -> 30.7 us.
+  __device__ __forceinline__ ConstTab<T> table() const {
+    return const_tab<T>(M.tab + (sizeof(T) == 8 ? 0 : M.proj_off + NP * NQ));
   }
-  template <int D, int TT>
-  __device__ __forceinline__ T Sd(int q, int i) const {
-    constexpr int Q = TT == 1 ? NQY : NQ;
-    constexpr auto& tb = ct::tab<NP, Q>;
-    return MEM ? T(M.tab[(TT == 1 && ENR ? L.Sdy : L.Sd) + q * NP + i]) : T(tb.Sd[q][i]);
-  }
+  // offsets of S, S' of the rule along a tangential direction
+  template <int TT>
+  static constexpr int S = TT == 1 && ENR ? L.Sy : L.S;
+  template <int TT>
+  static constexpr int Sd = TT == 1 && ENR ? L.Sdy : L.Sd;
 
   // own node layers of all six faces: value and d/dxi_D, one line each
   __device__ __forceinline__ void layers() {
@@ -938,6 +936,7 @@ struct CurvedFaces {
   template <int D>
   __device__ __forceinline__ void traces() {
     using DD = Dir<D>;
+    const ConstTab<T> tb = table();
     const bool wall0 = face_nb(M, ex, ey, ez, D, 0).wall, wall1 = face_nb(M, ex, ey, ez, D, 1).wall;
     for (int t = 255 - (int)threadIdx.x; t < 24 * NP; t += 256) {
       const int i2 = t % NP;
@@ -956,7 +955,7 @@ struct CurvedFaces {
       for (int q = 0; q < DD::Q1; ++q) {
         T v = 0;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) v += S<D, DD::T1>(q, i) * x[i];
+        for (int i = 0; i < NP; ++i) v += tb[S<DD::T1> + q * NP + i] * x[i];
         o[q] = v;
       }
       if (!dn) {
@@ -964,7 +963,7 @@ struct CurvedFaces {
         for (int q = 0; q < DD::Q1; ++q) {
           T v = 0;
 #pragma unroll
-          for (int i = 0; i < NP; ++i) v += Sd<D, DD::T1>(q, i) * x[i];
+          for (int i = 0; i < NP; ++i) v += tb[Sd<DD::T1> + q * NP + i] * x[i];
           o[DD::QN + q] = v;
         }
       }
@@ -975,6 +974,7 @@ struct CurvedFaces {
   template <int D>
   __device__ __forceinline__ void fields() {
     using DD = Dir<D>;
+    const ConstTab<T> tb = table();
     for (int t = threadIdx.x; t < 24 * DD::Q1; t += 256) {
       const int q1 = t % DD::Q1;
       int r = t / DD::Q1;
@@ -990,7 +990,7 @@ struct CurvedFaces {
       for (int q = 0; q < DD::Q2; ++q) {
         T v = 0;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) v += S<D, DD::T2>(q, i) * x[i];
+        for (int i = 0; i < NP; ++i) v += tb[S<DD::T2> + q * NP + i] * x[i];
         o[(h ? DD::TP : 0) + DD::Q1 * q] = v;
       }
       if (!h) {
@@ -998,7 +998,7 @@ struct CurvedFaces {
         for (int q = 0; q < DD::Q2; ++q) {
           T v = 0;
 #pragma unroll
-          for (int i = 0; i < NP; ++i) v += Sd<D, DD::T2>(q, i) * x[i];
+          for (int i = 0; i < NP; ++i) v += tb[Sd<DD::T2> + q * NP + i] * x[i];
           o[2 * DD::TP + DD::Q1 * q] = v;
         }
       } else {
@@ -1008,7 +1008,7 @@ struct CurvedFaces {
         for (int q = 0; q < DD::Q2; ++q) {
           T v = 0;
 #pragma unroll
-          for (int i = 0; i < NP; ++i) v += S<D, DD::T2>(q, i) * x[i];
+          for (int i = 0; i < NP; ++i) v += tb[S<DD::T2> + q * NP + i] * x[i];
           o[3 * DD::TP + DD::Q1 * q] = v;
         }
       }
@@ -1106,6 +1106,7 @@ struct CurvedFaces {
   template <int D>
   __device__ __forceinline__ void tests() {
     using DD = Dir<D>;
+    const ConstTab<T> tb = table();
     constexpr int FL = DD::FL, Q1 = DD::Q1, Q2 = DD::Q2;
     for (int t = threadIdx.x; t < 18 * Q1; t += 256) {
       const int q1 = t % Q1;
@@ -1121,7 +1122,7 @@ struct CurvedFaces {
       for (int i = 0; i < NP; ++i) {
         o[i] = 0;
 #pragma unroll
-        for (int q = 0; q < Q2; ++q) o[i] += S<D, DD::T2>(q, i) * x[q];
+        for (int q = 0; q < Q2; ++q) o[i] += tb[S<DD::T2> + q * NP + i] * x[q];
       }
       if (kind == 0) {
 #pragma unroll
@@ -1129,7 +1130,7 @@ struct CurvedFaces {
 #pragma unroll
         for (int i = 0; i < NP; ++i)
 #pragma unroll
-          for (int q = 0; q < Q2; ++q) o[i] += Sd<D, DD::T2>(q, i) * x[q];
+          for (int q = 0; q < Q2; ++q) o[i] += tb[Sd<DD::T2> + q * NP + i] * x[q];
       }
       T* b = TR + ((s * 3 + c) * 3 + kind) * DD::QN + q1;
 #pragma unroll
@@ -2035,7 +2036,7 @@ __host__ __device__ constexpr bool vel_use_affine() { return sizeof(T) == 4; }
 // cells 128: below that they spill.)
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, int LE = 1>
 __host__ __device__ constexpr int vel_wg_per_cu() {
-  if (CURVED) return sizeof(T) == 8 ? 2 : 4;  // FP32, k = 5: 0.90 ms with room for four, 1.05 ms for two
+  if (CURVED) return sizeof(T) == 8 ? 2 : 4;  // as many as the LDS holds at k = 5
   if (LE != 1) return ENR ? 2 : 3;  // general path; enriched cells hold 24 test-row sums
   if (!vel_use_affine<T>() || !AffShape<T, NP, NQ, NQY>::fits) return 3;
   const int by_lds = (160 * 1024) / AffShape<T, NP, NQ, NQY>::BYTES;
