@@ -872,8 +872,8 @@ struct CurvedFaces {
 
   // The 1-D tables in the kernel's precision, taken anew in every phase (see const_tab).  In FP32 a compile-time table
   // puts a literal into every FMA, 40 KB of code and 128 registers with spills at k = 5 (82 here): a mesh that gives a
-  // CU few cells waits for that code.  FP32 residual, k = 5: 8 x 4 x 4 cells 51.5 -> 44.4 us, 48 x 24 x 24 cells
-  // 896 -> 781 us; k = 3, 8 x 4 x 4 cells 32.5 -> 30.7 us.
+  // CU few cells waits for that code.  FP32 residual, k = 5: 8 x 4 x 4 cells 51.5 -> 44.8 us, 48 x 24 x 24 cells
+  // 894 -> 783 us; k = 3, 8 x 4 x 4 cells 32.4 -> 31.0 us.
   __device__ __forceinline__ ConstTab<T> table() const {
     return const_tab<T>(M.tab + (sizeof(T) == 8 ? 0 : M.proj_off + NP * NQ));
   }
@@ -1053,8 +1053,18 @@ struct CurvedFaces {
     T nv[3], wf;
     {
       const T x = geo[3 * D], y = geo[3 * D + 1], z = geo[3 * D + 2];
-      const T q = (s ? T(1) : T(-1)) / sqrt(x * x + y * y + z * z);
-      const T n[3] = {q * x, q * y, q * z};
+      const T sg = s ? T(1) : T(-1), nr = sqrt(x * x + y * y + z * z);
+      T n[3];
+      if constexpr (sizeof(T) == 4) {  // a rounding less than the product with the reciprocal
+        n[0] = sg * x / nr;
+        n[1] = sg * y / nr;
+        n[2] = sg * z / nr;
+      } else {
+        const T q = sg / nr;
+        n[0] = q * x;
+        n[1] = q * y;
+        n[2] = q * z;
+      }
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         const T o = pair_swap(n[d]);
@@ -1128,9 +1138,12 @@ struct CurvedFaces {
 #pragma unroll
         for (int q = 0; q < Q2; ++q) x[q] = fo[6 * FL + Q1 * q];
 #pragma unroll
-        for (int i = 0; i < NP; ++i)
+        for (int i = 0; i < NP; ++i) {
+          T w = 0;  // a sum of its own: behind the values' one its larger terms would round at both sums' size
 #pragma unroll
-          for (int q = 0; q < Q2; ++q) o[i] += tb[Sd<DD::T2> + q * NP + i] * x[q];
+          for (int q = 0; q < Q2; ++q) w += tb[Sd<DD::T2> + q * NP + i] * x[q];
+          o[i] += w;
+        }
       }
       T* b = TR + ((s * 3 + c) * 3 + kind) * DD::QN + q1;
 #pragma unroll
