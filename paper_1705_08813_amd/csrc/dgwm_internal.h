@@ -321,6 +321,9 @@ struct RegularLayers {
   int lo, nl, ilo, inl, xlo, xnl, xstep;
 };
 RegularLayers regular_layers(const dg_mesh* m);
+// the same for an operator whose general kernel takes the cells next to an enriched layer: up to `resident` cells without
+// enrichment it takes them all (inl = 0)
+RegularLayers split_layers(const dg_mesh* m, int64_t resident);
 // vorticity right-hand side b(v) = (v, curl u)_e and the wall term of the
 // pressure Neumann data, added into rhs (kern_step.hip)
 int launch_vorticity_rhs(const dg_mesh* m, const double* u, double* b, hipStream_t s);

@@ -32,6 +32,11 @@ namespace dgwm {
 namespace {
 
 constexpr int kDgThreads = 256;
+// Regular cells whose general divergence workgroups are resident at once (k = 5: five a CU; below: six or more).
+// Measured, all cells in one launch against interior and interface apart: 8 x 8 x 8 cells 20.3 / 23.9, 24.7 / 30.0 and
+// 27.5 / 32.2 us (k = 3, 4, 5), 16 x 8 x 16 cells 26.9 / 26.8, 34.2 / 35.8 and 47.3 / 40.8 us, 24 x 8 x 24 cells 42 / 36,
+// 57 / 47 and 88 / 70 us.
+constexpr int64_t div_resident(int np) { return 256 * (np >= 6 ? 5 : 6); }
 
 struct DgArgs {
   int nx, ny, nz, lower_slot, upper_slot, nslots, psi_pts, fully_periodic;
@@ -491,7 +496,7 @@ int launch_divgrad(const dg_mesh* m, bool divergence, const double* in, double* 
   A.out = out;
   // cells without enrichment take the 1-D operators (launch_divgrad_regular); u of an enriched neighbour enters the
   // divergence by quadrature, so the layers next to an enriched one keep the general kernel
-  const RegularLayers L = regular_layers(m);
+  const RegularLayers L = divergence ? split_layers(m, div_resident(m->np_u)) : regular_layers(m);
   A.layer_step = L.xstep;
   const int64_t nreg = divergence ? (int64_t)m->P.nx * L.xnl * m->P.nz : 0;
   // without enriched cells nq_wn is irrelevant

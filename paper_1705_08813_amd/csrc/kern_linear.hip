@@ -743,6 +743,20 @@ RegularLayers regular_layers(const dg_mesh* m) {
   return L;
 }
 
+// A launch of its own for the cells away from the enriched layers costs 5 us or more.  While the general kernel's
+// workgroups (one a cell) of all regular cells are resident at once, they take no longer than those of the interface
+// cells alone, so `resident` is 256 CUs times the kernel's workgroups a CU.
+RegularLayers split_layers(const dg_mesh* m, int64_t resident) {
+  RegularLayers L = regular_layers(m);
+  if (L.xnl > 0 && L.inl > 0 && (int64_t)m->P.nx * L.nl * m->P.nz <= resident) {
+    L.inl = 0;
+    L.xlo = L.lo;
+    L.xnl = L.nl;
+    L.xstep = 1;
+  }
+  return L;
+}
+
 int launch_viscous_regular(const dg_mesh* m, const double* u, double* out, int lo, int nl, bool inverse_mass,
                            hipStream_t s) {
   if (nl <= 0) return DG_OK;
