@@ -2137,13 +2137,26 @@ int launch_vel_t(const dg_mesh* m, const MeshDev& M, const void* u, void* r, boo
   return check_hip(hipGetLastError(), "velocity kernel launch");
 }
 
+// Degree-1 enrichment weights: regular cells whose general workgroups are
+// resident at once (registers: three a CU for the FP64 residual, four for FP32
+// and for the viscous operator).  Measured, all cells in one launch against
+// interior and interface apart, k = 4: FP64 residual 55.9 / 62.9, 75.9 / 73.9 and
+// 87.8 / 79.3 us on 8 x 8 x 8, 12 x 8 x 12 and 16 x 8 x 16 cells (384, 864 and 1,536
+// regular ones), FP32 48.4 / 55.0, 53.7 / 59.4 and 67.4 / 61.3 us, viscous operator
+// 56.5 / 61.8, 67.3 / 69.9 and 85.3 / 76.1 us.
+template <typename T, bool MS>
+constexpr int64_t l1_resident() {
+  return 256 * (sizeof(T) == 8 && !MS ? 3 : 4);
+}
+
 // Degree-1 enrichment weights (flat meshes): the cells next to an enriched
-// layer take the general kernel, which reads the neighbours' 24 coefficients.
+// layer, or all of a small mesh (split_layers), take the general kernel, which
+// reads the neighbours' 24 coefficients.
 template <typename T, int NP, int NQ, int NQW>
 int launch_vel_l1_t(const dg_mesh* m, const MeshDev& M, const void* u, void* r, bool convective_only, hipStream_t s) {
   const T* uu = static_cast<const T*>(u);
   T* rr = static_cast<T*>(r);
-  const RegularLayers L = regular_layers(m);
+  const RegularLayers L = split_layers(m, l1_resident<T, false>());
   if (int rc = launch_residual_regular<T>(m, uu, rr, L.ilo, L.inl, !convective_only, s)) return rc;
   if (L.xnl > 0)
     hipLaunchKernelGGL((vel_kernel<T, NP, NQ, NQ, false, false, 8>),
@@ -2244,8 +2257,8 @@ bool velocity_l1_supported(int np, int nq, int nqy) {
 
 const char* velocity_l1_combos() { return "(3,4,8) (4,4,8) (4,5,8) (5,7,8)"; }
 
-// Enriched cells and, with degree-1 weights, the cells next to them; the other
-// cells take launch_viscous_regular.
+// Enriched cells and, with degree-1 weights, the cells next to them (all cells
+// of a small mesh); the other cells take launch_viscous_regular.
 template <int NP, int NQ, int NQW, int LE>
 static int launch_visc_ms_t(const dg_mesh* m, const MeshDev& M, const RegularLayers& L, const double* u, double* r,
                             hipStream_t s) {
@@ -2265,7 +2278,7 @@ int launch_viscous_multiscale(const dg_mesh* m, const double* nut, const double*
                               bool inverse_mass) {
   MeshDev M = velocity_meshdev(m);
   M.nut = nut;
-  const RegularLayers L = regular_layers(m);
+  const RegularLayers L = m->nle == 1 ? regular_layers(m) : split_layers(m, l1_resident<double, true>());
   int rc = m->nle == 1 ? launch_viscous_regular(m, u, out, L.lo, L.nl, inverse_mass, s)
                        : launch_viscous_regular(m, u, out, L.ilo, L.inl, inverse_mass, s);
   if (rc || m->nenr == 0) return rc;
