@@ -32,18 +32,24 @@ void legendre_pd(int n, double t, double& p, double& dp) {
   dp = n * (t * pc - pm1) / (t * t - 1.0);
 }
 
-// Barycentric weights of a node set.
-std::vector<double> bary_weights(const double* x, int n) {
-  std::vector<double> lam(n, 1.0);
-  for (int i = 0; i < n; ++i)
-    for (int j = 0; j < n; ++j)
-      if (j != i) lam[i] /= (x[i] - x[j]);
-  return lam;
-}
+// A node set with its barycentric weights.
+struct Nodes {
+  const double* x;
+  int n;
+  double lam[kMaxQ];
+  Nodes(const double* x_, int n_) : x(x_), n(n_) {
+    for (int i = 0; i < n; ++i) {
+      lam[i] = 1.0;
+      for (int j = 0; j < n; ++j)
+        if (j != i) lam[i] /= (x[i] - x[j]);
+    }
+  }
+};
 
-// Values and first derivatives of the Lagrange basis through x at t.
-void lagrange_eval(const double* x, int n, double t, double* v, double* d) {
-  std::vector<double> lam = bary_weights(x, n);
+// Values and first derivatives of the Lagrange basis through the nodes at t.
+void lagrange_eval(const Nodes& N, double t, double* v, double* d) {
+  const double *x = N.x, *lam = N.lam;
+  const int n = N.n;
   for (int i = 0; i < n; ++i) {
     if (t == x[i]) {
       // at a node: cardinal values; N_j'(x_i) = (lam_j/lam_i)/(x_i - x_j),
@@ -116,17 +122,19 @@ void fill_tables(int np, int nq, int nqy, double* out) {
   const TabLayout L = tab_layout(np, nq, nqy);
   double gl[kMaxP];
   lobatto_nodes(np, gl);
+  const Nodes B(gl, np);
   auto rule = [&](int n, int oS, int oSd, int oD, int ow, int og) {
     double g[kMaxQ], w[kMaxQ], v[kMaxQ], d[kMaxQ];
     gauss_rule(n, g, w);
+    const Nodes G(g, n);
     for (int q = 0; q < n; ++q) {
-      lagrange_eval(gl, np, g[q], v, d);
+      lagrange_eval(B, g[q], v, d);
       for (int i = 0; i < np; ++i) {
         out[oS + q * np + i] = v[i];
         out[oSd + q * np + i] = d[i];
       }
       // collocation derivative through the Gauss points themselves
-      lagrange_eval(g, n, g[q], v, d);
+      lagrange_eval(G, g[q], v, d);
       for (int r = 0; r < n; ++r) out[oD + q * n + r] = d[r];
       out[ow + q] = w[q];
       out[og + q] = g[q];
@@ -135,9 +143,9 @@ void fill_tables(int np, int nq, int nqy, double* out) {
   rule(nq, L.S, L.Sd, L.D, L.w, L.g);
   rule(nqy, L.Sy, L.Sdy, L.Dy, L.wy, L.gy);
   double v[kMaxP], d[kMaxP];
-  lagrange_eval(gl, np, 0.0, v, d);
+  lagrange_eval(B, 0.0, v, d);
   for (int i = 0; i < np; ++i) out[L.nd0 + i] = d[i];
-  lagrange_eval(gl, np, 1.0, v, d);
+  lagrange_eval(B, 1.0, v, d);
   for (int i = 0; i < np; ++i) out[L.nd1 + i] = d[i];
   for (int i = 0; i < np; ++i) out[L.gl + i] = gl[i];
 }
@@ -146,8 +154,9 @@ void fill_poisson_ops(int np, int nq, double* out) {
   const PoiOps o = poi_ops(np);
   double gl[kMaxP], g[kMaxQ], w[kMaxQ], v[kMaxQ][kMaxP], d[kMaxQ][kMaxP];
   lobatto_nodes(np, gl);
+  const Nodes B(gl, np);
   gauss_rule(nq, g, w);
-  for (int q = 0; q < nq; ++q) lagrange_eval(gl, np, g[q], v[q], d[q]);
+  for (int q = 0; q < nq; ++q) lagrange_eval(B, g[q], v[q], d[q]);
   for (int i = 0; i < np; ++i)
     for (int j = 0; j < np; ++j) {
       double m = 0, k = 0;
@@ -159,9 +168,9 @@ void fill_poisson_ops(int np, int nq, double* out) {
       out[o.K + i * np + j] = k;
     }
   double v0[kMaxP], d0[kMaxP];
-  lagrange_eval(gl, np, 0.0, v0, d0);
+  lagrange_eval(B, 0.0, v0, d0);
   for (int i = 0; i < np; ++i) out[o.nd0 + i] = d0[i];
-  lagrange_eval(gl, np, 1.0, v0, d0);
+  lagrange_eval(B, 1.0, v0, d0);
   for (int i = 0; i < np; ++i) out[o.nd1 + i] = d0[i];
   float* f = reinterpret_cast<float*>(out + o.f32);
   for (int i = 0; i < o.n; ++i) f[i] = (float)out[i];
@@ -201,10 +210,11 @@ void invert(int np, const R (&M)[kMaxP][kMaxP], R (&I)[kMaxP][kMaxP]) {
 void fill_projection(int np, int nq, double* out) {
   double gl[kMaxP], g[kMaxQ], w[kMaxQ], v[kMaxQ][kMaxP], d[kMaxP];
   lobatto_nodes(np, gl);
+  const Nodes B(gl, np);
   gauss_rule(nq, g, w);
   R M[kMaxP][kMaxP] = {}, I[kMaxP][kMaxP];
   for (int q = 0; q < nq; ++q) {
-    lagrange_eval(gl, np, g[q], v[q], d);
+    lagrange_eval(B, g[q], v[q], d);
     for (int i = 0; i < np; ++i)
       for (int j = 0; j < np; ++j) M[i][j] += (R)w[q] * v[q][i] * v[q][j];
   }
@@ -221,10 +231,11 @@ void fill_lin_ops(int np, double* out) {
   const LinOps o = lin_ops(np);
   double gl[kMaxP], g[kMaxQ], w[kMaxQ], v[kMaxP], d[kMaxP];
   lobatto_nodes(np, gl);
+  const Nodes B(gl, np);
   gauss_rule(np, g, w);  // exact for the products of two basis functions
   R M[kMaxP][kMaxP] = {}, K[kMaxP][kMaxP] = {}, C[kMaxP][kMaxP] = {}, I[kMaxP][kMaxP];
   for (int q = 0; q < np; ++q) {
-    lagrange_eval(gl, np, g[q], v, d);
+    lagrange_eval(B, g[q], v, d);
     for (int i = 0; i < np; ++i)
       for (int j = 0; j < np; ++j) {
         M[i][j] += (R)w[q] * v[i] * v[j];
@@ -234,10 +245,10 @@ void fill_lin_ops(int np, double* out) {
   }
   invert(np, M, I);
   double nd0[kMaxP], nd1[kMaxP];
-  lagrange_eval(gl, np, 0.0, v, nd0);
-  lagrange_eval(gl, np, 1.0, v, nd1);
+  lagrange_eval(B, 0.0, v, nd0);
+  lagrange_eval(B, 1.0, v, nd1);
   for (int i = 0; i < np; ++i) {
-    lagrange_eval(gl, np, gl[i], v, d);
+    lagrange_eval(B, gl[i], v, d);
     R a0 = 0, a1 = 0;
     for (int j = 0; j < np; ++j) {
       out[o.M + i * np + j] = (double)M[i][j];
@@ -266,20 +277,24 @@ void fill_lin_ops(int np, double* out) {
 void fill_mix_ops(int npu, int npp, double* out) {
   const MixOps o = mix_ops(npu, npp);
   const int nq = npu > npp ? npu : npp;  // exact for the products
-  double gu[kMaxP], gp[kMaxP], g[kMaxQ], w[kMaxQ], vu[kMaxP], du[kMaxP], vp[kMaxP], dp[kMaxP];
+  double gu[kMaxP], gp[kMaxP], g[kMaxQ], w[kMaxQ];
+  double vu[kMaxP][kMaxP], du[kMaxP][kMaxP], vp[kMaxP][kMaxP], dp[kMaxP][kMaxP];
   lobatto_nodes(npu, gu);
   lobatto_nodes(npp, gp);
+  const Nodes U(gu, npu), P(gp, npp);
   gauss_rule(nq, g, w);
+  for (int q = 0; q < nq; ++q) {
+    lagrange_eval(U, g[q], vu[q], du[q]);
+    lagrange_eval(P, g[q], vp[q], dp[q]);
+  }
   for (int i = 0; i < npu; ++i)
     for (int a = 0; a < npp; ++a) {
       const double ends = (i == npu - 1 && a == npp - 1 ? 0.5 : 0.0) - (i == 0 && a == 0 ? 0.5 : 0.0);
       long double m = 0, cu = 0, cp = 0;
       for (int q = 0; q < nq; ++q) {
-        lagrange_eval(gu, npu, g[q], vu, du);
-        lagrange_eval(gp, npp, g[q], vp, dp);
-        m += (long double)w[q] * vu[i] * vp[a];
-        cu += (long double)w[q] * du[i] * vp[a];
-        cp += (long double)w[q] * dp[a] * vu[i];
+        m += (long double)w[q] * vu[q][i] * vp[q][a];
+        cu += (long double)w[q] * du[q][i] * vp[q][a];
+        cp += (long double)w[q] * dp[q][a] * vu[q][i];
       }
       out[o.Mup + i * npp + a] = (double)m;
       out[o.Gu + i * npp + a] = (double)(ends - cu);
