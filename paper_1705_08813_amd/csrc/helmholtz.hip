@@ -43,7 +43,8 @@ constexpr int kHMaxRestart = 100;
 // per vector in registers: 16 at a time (32 cost a third of the rate, 153
 // registers).  The update holds only scalars: 32, so that a cycle of 30 reads
 // and writes the candidate and the new vector once per step (64 x 32 x 32 mesh,
-// k = 4, 57 steps: 36.0 ms against 38.4 ms with 16).
+// k = 4, 57 steps: 36.0 ms against 38.4 ms with 16).  A launch of at most 16
+// vectors keeps the kernel of 16, which does not wait for 32 pairs of scalars.
 constexpr int kHChunk = 16;
 constexpr int kHUpdChunk = 32;
 // device scalars: projections of the candidate (s, from 0) and of the new
@@ -173,13 +174,14 @@ __global__ __launch_bounds__(kHThreads) void h_mfinal(const double* __restrict__
 // (hw) w -= sum_k z_k V_{k0+k}, with s and z on the device; in the last chunk
 // also u = u / beta (the finished basis vector v_j) and w = w / beta - g2 u
 // (the next candidate; ib = 1 / beta).
+template <int CHUNK>
 __global__ __launch_bounds__(kHThreads) void h_dupdate(double* __restrict__ u, double* __restrict__ w, int hw,
                                                        const double* __restrict__ V, int64_t stride, int k0, int nk,
                                                        const double* __restrict__ sv, const double* __restrict__ zv,
                                                        int64_t n, int last, double ib, double g2) {
-  double cs[kHUpdChunk], cz[kHUpdChunk];
+  double cs[CHUNK], cz[CHUNK];
 #pragma unroll
-  for (int k = 0; k < kHUpdChunk; ++k) {
+  for (int k = 0; k < CHUNK; ++k) {
     cs[k] = k < nk ? sv[k0 + k] : 0.0;
     cz[k] = (hw && k < nk) ? zv[k0 + k] : 0.0;
   }
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(kHThreads) void h_dupdate(double* __restrict__ u, d
     double2 a = reinterpret_cast<const double2*>(u)[i];
     double2 c = hw ? reinterpret_cast<const double2*>(w)[i] : double2{0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < kHUpdChunk; ++k)
+    for (int k = 0; k < CHUNK; ++k)
       if (k < nk) {
         const double2 v = reinterpret_cast<const double2*>(v0 + k * stride)[i];
         a.x -= cs[k] * v.x;
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(kHThreads) void h_dupdate(double* __restrict__ u, d
   if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {
     double a = u[n - 1], c = hw ? w[n - 1] : 0.0;
 #pragma unroll
-    for (int k = 0; k < kHUpdChunk; ++k)
+    for (int k = 0; k < CHUNK; ++k)
       if (k < nk) {
         const double v = v0[k * stride + n - 1];
         a -= cs[k] * v;
@@ -301,9 +303,13 @@ struct Gm {
     double* u = v(j);
     double* w = hw ? v(j + 1) : nullptr;
     for (int k0 = 0; k0 == 0 || k0 < j; k0 += kHUpdChunk) {
-      const int nk = std::min(kHUpdChunk, j - k0);
-      hipLaunchKernelGGL(h_dupdate, dim3(h_blocks(n)), dim3(kHThreads), 0, s, u, w, hw ? 1 : 0, V, stride, k0, nk,
-                         sc, sc + kHZ, n, (k0 + kHUpdChunk >= j) ? 1 : 0, ib, g2);
+      const int nk = std::min(kHUpdChunk, j - k0), last = k0 + kHUpdChunk >= j;
+      if (nk <= kHChunk)
+        hipLaunchKernelGGL(h_dupdate<kHChunk>, dim3(h_blocks(n)), dim3(kHThreads), 0, s, u, w, hw ? 1 : 0, V, stride, k0,
+                           nk, sc, sc + kHZ, n, last, ib, g2);
+      else
+        hipLaunchKernelGGL(h_dupdate<kHUpdChunk>, dim3(h_blocks(n)), dim3(kHThreads), 0, s, u, w, hw ? 1 : 0, V, stride,
+                           k0, nk, sc, sc + kHZ, n, last, ib, g2);
     }
     return check_hip(hipGetLastError(), "helmholtz projection update");
   }
