@@ -245,15 +245,20 @@ size_t block_entries(int np) {
 
 }  // namespace
 
-// K^{-1}, per layer slot the blocks and eigenvalues, the int32 layer map; at
-// least the two dense n x n tables of one layer are reserved, the size that
-// callers who leave the step tables out can count on saving.
+// K^{-1}, per layer slot the blocks and eigenvalues, the int32 layer map.
+static size_t table_doubles(const dg_mesh& m, int ns) {
+  const size_t n = 3 * (size_t)m.np_u * m.np_u * m.np_u;
+  return (size_t)m.np_u * m.np_u + (size_t)ns * (2 * block_entries(m.np_u) + n) + (m.P.ny + 1) / 2;
+}
+
+// Doubles reserved in the mesh workspace: the tables, and at least the size of
+// one layer's dense n x n pair, which callers who leave the step tables out
+// count on saving.  What is beyond the tables is neither formed nor written.
 size_t spectral_table_doubles(const dg_mesh& m) {
   const int ns = spectral_layers(m, nullptr, nullptr);
   if (ns == 0) return 0;
   const size_t n = 3 * (size_t)m.np_u * m.np_u * m.np_u;
-  const size_t need = (size_t)m.np_u * m.np_u + (size_t)ns * (2 * block_entries(m.np_u) + n) + (m.P.ny + 1) / 2;
-  return std::max(need, 2 * n * n + n);
+  return std::max(table_doubles(m, ns), 2 * n * n + n);
 }
 
 // Host: 1-D factors, whitened div-div forms, their eigendecompositions; copies
@@ -284,7 +289,7 @@ static int build_spectral_tables(const dg_mesh* m, hipStream_t s) {
   cholesky(np, K, C);
   lower_inverse(np, C, Ci);
   const size_t nz = (size_t)cl.zn, head = (size_t)np * np, per = 2 * nz + n;
-  std::vector<double> host(spectral_table_doubles(*m), 0.0);
+  std::vector<double> host(table_doubles(*m, ns), 0.0);
   double* Kinv = host.data();
   for (int a = 0; a < np; ++a)
     for (int i = 0; i < np; ++i) {
