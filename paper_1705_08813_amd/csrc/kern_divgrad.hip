@@ -15,7 +15,9 @@
 // enriched cells) and of its faces (x- and z-faces take the cell's
 // wall-normal rule, which every neighbour in the same layer shares).
 //
-// One workgroup per cell; the output block of the cell is accumulated in LDS
+// Cells without enrichment take 1-D operators (launch_divgrad_regular), those
+// next to an enriched layer for the gradient only.  The kernels here: one
+// workgroup per cell; the output block of the cell is accumulated in LDS
 // (volume term first, then the faces direction by direction) and written
 // once, so every output has one writer.  Values at points come from
 // sum-factorized interpolation sweeps, test-function integrals from the
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(kDgThreads) void divergence_kernel(const DgArgs A, 
 
 // Faces of direction D: n_D {{p}} at the face points, integrated against the
 // velocity face layer of component D (and psi for the enrichment row D).
-template <int NPU, int NPP, int NQ, int NQY, bool ENR, int LE, int D>
+template <int NPU, int NPP, int NQ, int NQY, int LE, int D>
 __device__ __forceinline__ void grad_faces(const DgArgs& A, const CellGeo& g, const double* sp, const double* nl,
                                            const int64_t* nbf, double* w0, double* w1, double* acc, double* red,
                                            double* accE, int tid) {
@@ -317,7 +319,6 @@ __device__ __forceinline__ void grad_faces(const DgArgs& A, const CellGeo& g, co
   constexpr int Q1 = T1 == 1 ? NQY : NQ, Q2 = T2 == 1 ? NQY : NQ;
   constexpr auto& tb1 = ct::tab<NPU, Q1>;
   constexpr auto& tb2 = ct::tab<NPU, Q2>;
-  constexpr int NW = kDgThreads / 64;
   // pressure layers [s][side][l1 + NPP l2]; a wall repeats the own layer (p+ = p-)
   for (int it = tid; it < 4 * NP2; it += kDgThreads) {
     const int r = it / NP2, l = it - r * NP2, s = r >> 1;
@@ -342,28 +343,22 @@ __device__ __forceinline__ void grad_faces(const DgArgs& A, const CellGeo& g, co
     const double fl = tb1.w[q1] * tb2.w[q2] * area * (s ? 0.5 : -0.5) *
                       (w0[(s * 2) * Q1 * Q2 + pt] + w0[(s * 2 + 1) * Q1 * Q2 + pt]);
     w1[it] = fl;
-    if (ENR) {
-      const double pf = A.psi[(g.enr * A.psi_pts + A.psi_off[1 + 2 * D + s] + pt) * 4] * fl;
-      if (LE == 1) {
-        ve[0] += pf;
-      } else {
+    const double pf = A.psi[(g.enr * A.psi_pts + A.psi_off[1 + 2 * D + s] + pt) * 4] * fl;
+    if (LE == 1) {
+      ve[0] += pf;
+    } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const double f = vtx_face(j, tb1.g[q1], tb2.g[q2]) * pf;
-          ve[j] += s ? 0.0 : f;
-          ve[4 + j] += s ? f : 0.0;
-        }
+      for (int j = 0; j < 4; ++j) {
+        const double f = vtx_face(j, tb1.g[q1], tb2.g[q2]) * pf;
+        ve[j] += s ? 0.0 : f;
+        ve[4 + j] += s ? f : 0.0;
       }
     }
   }
-  if (ENR) {
-    block_sum_n<NE>(ve, red);  // (its barrier also publishes w1)
-    if (tid < NE) {
-      if (LE == 1) accE[D] += ve[0];
-      else accE[D * LE + vtx_index<D>(tid >> 2, tid & 3)] += ve[0];
-    }
-  } else {
-    __syncthreads();
+  block_sum_n<NE>(ve, red);  // (its barrier also publishes w1)
+  if (tid < NE) {
+    if (LE == 1) accE[D] += ve[0];
+    else accE[D * LE + vtx_index<D>(tid >> 2, tid & 3)] += ve[0];
   }
   sweep_c<0, Q1, Q2, 1, NPU, true, false, MS<NPU, Q1>>(w1, Q1 * Q2, w0, NPU * Q2, 1.0, 2);
   __syncthreads();
@@ -376,8 +371,9 @@ __device__ __forceinline__ void grad_faces(const DgArgs& A, const CellGeo& g, co
   __syncthreads();
 }
 
-template <int NPU, int NPP, int NQ, int NQY, bool ENR, int LE>
-__global__ __launch_bounds__(kDgThreads) void gradient_kernel(const DgArgs A, int layer_lo, int nlayers) {
+// The enriched cells (the others take launch_divgrad_regular), one workgroup each.
+template <int NPU, int NPP, int NQ, int NQY, int LE>
+__global__ __launch_bounds__(kDgThreads) void gradient_kernel(const DgArgs A) {
   constexpr int NU3 = NPU * NPU * NPU, NP3 = NPP * NPP * NPP, NPT = NQ * NQY * NQ, NP2 = NPP * NPP;
   constexpr auto& tq = ct::tab<NPU, NQ>;
   constexpr auto& ty = ct::tab<NPU, NQY>;
@@ -389,7 +385,7 @@ __global__ __launch_bounds__(kDgThreads) void gradient_kernel(const DgArgs A, in
   __shared__ double red[3 * LE * NW];
   __shared__ double accE[3 * LE];                // enrichment rows [c][B]
   const int tid = threadIdx.x;
-  const CellGeo g = cell_of_block<ENR>(A, blockIdx.x, layer_lo, nlayers);
+  const CellGeo g = cell_of_block<true>(A, blockIdx.x, 0, 0);
   const int64_t e = g.e;
   int64_t nbf[6];
 #pragma unroll
@@ -420,33 +416,27 @@ __global__ __launch_bounds__(kDgThreads) void gradient_kernel(const DgArgs A, in
   for (int q = tid; q < NPT; q += kDgThreads) {
     const int qx = q % NQ, qy = (q / NQ) % NQY, qz = q / (NQ * NQY);
     const double v = -tq.w[qx] * ty.w[qy] * tq.w[qz] * detJ * w0[q];
-    if (ENR) {
-      const double* ps = A.psi + (g.enr * A.psi_pts + q) * 4;
-      if (LE == 1) {
-        ve[0] += ps[1] * v;
-        ve[1] += ps[2] * v;
-        ve[2] += ps[3] * v;
-      } else {
-        const double x[3] = {tq.g[qx], ty.g[qy], tq.g[qz]};
+    const double* ps = A.psi + (g.enr * A.psi_pts + q) * 4;
+    if (LE == 1) {
+      ve[0] += ps[1] * v;
+      ve[1] += ps[2] * v;
+      ve[2] += ps[3] * v;
+    } else {
+      const double x[3] = {tq.g[qx], ty.g[qy], tq.g[qz]};
 #pragma unroll
-        for (int B = 0; B < LE; ++B) {
-          double dd[3];
-          const double nb = vtx(B, x, dd);
+      for (int B = 0; B < LE; ++B) {
+        double dd[3];
+        const double nb = vtx(B, x, dd);
 #pragma unroll
-          for (int c = 0; c < 3; ++c) ve[c * LE + B] += (nb * ps[1 + c] + ps[0] * dd[c] / g.h[c]) * v;
-        }
+        for (int c = 0; c < 3; ++c) ve[c * LE + B] += (nb * ps[1 + c] + ps[0] * dd[c] / g.h[c]) * v;
       }
     }
     w1[q] = v / g.h[0];
     w1[NPT + q] = v / g.h[1];
     w1[2 * NPT + q] = v / g.h[2];
   }
-  if (ENR) {
-    block_sum_n<3 * LE>(ve, red);  // (its barrier also publishes w1)
-    if (tid < 3 * LE) accE[tid] = ve[0];
-  } else {
-    __syncthreads();
-  }
+  block_sum_n<3 * LE>(ve, red);  // (its barrier also publishes w1)
+  if (tid < 3 * LE) accE[tid] = ve[0];
   // component c tested with d_c N^u; the three sweeps of a phase use separate wavefronts
   sweep_c<0, NQ, NQY, NQ, NPU, true, false, MD<NPU, NQ>>(w1, NPT, w0, NPT, 1.0, 1, 0);
   sweep_c<0, NQ, NQY, NQ, NPU, true, false, MS<NPU, NQ>>(w1 + NPT, NPT, w0 + NPT, NPT, 1.0, 1, 64);
@@ -461,12 +451,12 @@ __global__ __launch_bounds__(kDgThreads) void gradient_kernel(const DgArgs A, in
   sweep_c<2, NPU, NPU, NQ, NPU, true, false, MD<NPU, NQ>>(w1 + 2 * NPT, NPT, acc + 2 * NU3, NU3, 1.0, 1, 128);
   __syncthreads();
   // ---- faces
-  grad_faces<NPU, NPP, NQ, NQY, ENR, LE, 0>(A, g, sp, nl, nbf, w0, w1, acc, red, accE, tid);
-  grad_faces<NPU, NPP, NQ, NQY, ENR, LE, 1>(A, g, sp, nl, nbf, w0, w1, acc, red, accE, tid);
-  grad_faces<NPU, NPP, NQ, NQY, ENR, LE, 2>(A, g, sp, nl, nbf, w0, w1, acc, red, accE, tid);
+  grad_faces<NPU, NPP, NQ, NQY, LE, 0>(A, g, sp, nl, nbf, w0, w1, acc, red, accE, tid);
+  grad_faces<NPU, NPP, NQ, NQY, LE, 1>(A, g, sp, nl, nbf, w0, w1, acc, red, accE, tid);
+  grad_faces<NPU, NPP, NQ, NQY, LE, 2>(A, g, sp, nl, nbf, w0, w1, acc, red, accE, tid);
   double* oe = A.out + e * 3 * NU3;
   for (int B = tid; B < 3 * NU3; B += kDgThreads) oe[B] = acc[B];
-  if (ENR && tid < 3 * LE) A.out[A.ncell * 3 * NU3 + g.enr * 3 * LE + tid] = accE[tid];
+  if (tid < 3 * LE) A.out[A.ncell * 3 * NU3 + g.enr * 3 * LE + tid] = accE[tid];
 }
 
 }  // namespace
@@ -502,17 +492,19 @@ int launch_divgrad(const dg_mesh* m, bool divergence, const double* in, double* 
   // without enriched cells nq_wn is irrelevant
   const bool any_w = m->nenr == 0;
   const int nqw = m->P.nq_wn;
-#define LAUNCH(KER, pu, pp, q, w, ENRV, LEV, grid, lo_, nl_)                                            \
-  hipLaunchKernelGGL((KER<pu, pp, q, w, ENRV, LEV>), dim3((unsigned)(grid)), dim3(kDgThreads), 0, s, A, lo_, nl_)
+#define DIVERGENCE(pu, pp, q, w, ENRV, LEV, grid, lo_, nl_)                                               \
+  hipLaunchKernelGGL((divergence_kernel<pu, pp, q, w, ENRV, LEV>), dim3((unsigned)(grid)), dim3(kDgThreads), 0, s, A, \
+                     lo_, nl_)
 #define RUN(LEV, pu, pp, q, w)                                                                           \
   {                                                                                                      \
     int rc = divergence ? launch_divgrad_regular(m, true, in, out, L.ilo, L.inl, s)                      \
                         : launch_divgrad_regular(m, false, in, out, L.lo, L.nl, s);                      \
     if (rc) return rc;                                                                                   \
-    if (nreg > 0) LAUNCH(divergence_kernel, pu, pp, q, q, false, LEV, nreg, L.xlo, L.xnl);                \
+    if (nreg > 0) DIVERGENCE(pu, pp, q, q, false, LEV, nreg, L.xlo, L.xnl);                              \
     if (m->nenr > 0) {                                                                                   \
-      if (divergence) LAUNCH(divergence_kernel, pu, pp, q, w, true, LEV, m->nenr, 0, 0);                  \
-      else LAUNCH(gradient_kernel, pu, pp, q, w, true, LEV, m->nenr, 0, 0);                               \
+      if (divergence) DIVERGENCE(pu, pp, q, w, true, LEV, m->nenr, 0, 0);                                \
+      else                                                                                               \
+        hipLaunchKernelGGL((gradient_kernel<pu, pp, q, w, LEV>), dim3((unsigned)m->nenr), dim3(kDgThreads), 0, s, A); \
     }                                                                                                    \
     return check_hip(hipGetLastError(), "divergence/gradient kernel launch");                            \
   }
@@ -524,7 +516,7 @@ int launch_divgrad(const dg_mesh* m, bool divergence, const double* in, double* 
   DG_DG_COMBOS(X)
 #undef X
 #undef RUN
-#undef LAUNCH
+#undef DIVERGENCE
   return set_error(DG_ERR_UNSUPPORTED,
                    "pressure gradient / velocity divergence: (k_u+1, k_p+1, nq_u, nq_wn) combination not compiled");
 }

@@ -1362,9 +1362,9 @@ __device__ __forceinline__ void aff_nb_traces(const T* s_nl, const T* s_tab, T* 
 // fv = {{u (x) u}} n + Lambda/2 [u] - {{2 nu eps(u)}} n + tau nu [u] and
 // F_g[c][D] = -theta nu sym([u] (x) n)_{cD}, weighted by the face weight and
 // written back into FL in place: [0..2] w fv_c, [3..5] w F_g[c][D].
-// Enriched cells add the psi parts of both sides and the face terms of their
-// enrichment test rows to rt.
-template <typename T, int NP, int NQ, int NQY, bool ENR, int D, int S>
+// Adds the psi parts of both sides and the face terms of the cell's enrichment
+// test rows to rt.
+template <typename T, int NP, int NQ, int NQY, int D, int S>
 __device__ __forceinline__ void aff_flux(const MeshDev& M, const T* s_val, const T* s_grad, T* FL, const T* s_ut,
                                          const T* s_nut, bool wall, int64_t enr_nb, T tau, int64_t enr, T ht1, T ht2,
                                          T rt[3], int tofs) {
@@ -1407,18 +1407,12 @@ __device__ __forceinline__ void aff_flux(const MeshDev& M, const T* s_val, const
         sp[c] = fo[(3 + c) * FP];
       }
     }
-    T psim = 0, gpsim[3] = {0, 0, 0};
-    if (ENR) {
-      const double* ps = M.psi + ((size_t)enr * M.psi_pts + M.psi_off[1 + f] + pt) * 4;
-      psim = T(ps[0]);
-      gpsim[0] = T(ps[1]);
-      gpsim[1] = T(ps[2]);
-      gpsim[2] = T(ps[3]);
+    const double* po = M.psi + ((size_t)enr * M.psi_pts + M.psi_off[1 + f] + pt) * 4;
+    const T psim = T(po[0]), gpsim[3] = {T(po[1]), T(po[2]), T(po[3])};
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        um[c] += psim * s_ut[c];
-        sm[c] += s_ut[c] * gpsim[D] + s_ut[D] * gpsim[c];
-      }
+    for (int c = 0; c < 3; ++c) {
+      um[c] += psim * s_ut[c];
+      sm[c] += s_ut[c] * gpsim[D] + s_ut[D] * gpsim[c];
     }
     if (wall) {
 #pragma unroll
@@ -1453,9 +1447,9 @@ __device__ __forceinline__ void aff_flux(const MeshDev& M, const T* s_val, const
       Fg[c] = (c == D ? -T(2) : -T(1)) * hth * jmp;
       fo[c * FP] = wf * fv;
       fo[(3 + c) * FP] = wf * Fg[c];
-      if (ENR) rt[c] += wf * (psim * fv + Fg[c] * gpsim[D]);
+      rt[c] += wf * (psim * fv + Fg[c] * gpsim[D]);
     }
-    if (ENR) rt[D] += wf * (Fg[T1] * gpsim[T1] + Fg[T2] * gpsim[T2]);
+    rt[D] += wf * (Fg[T1] * gpsim[T1] + Fg[T2] * gpsim[T2]);
   }
 }
 
@@ -1481,9 +1475,10 @@ __device__ __forceinline__ void aff_spread(const T* FL, const T* s_ext, int qx, 
   }
 }
 
-template <typename T, int NP, int NQ, int NQY, bool ENR>
-__device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __restrict__ u, T* __restrict__ r, int b,
-                                                int layer_lo, int nlayers) {
+// One enriched cell, FP32; b: its enriched index.
+template <typename T, int NP, int NQ, int NQY>
+__device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __restrict__ u, T* __restrict__ r, int b) {
+  static_assert(sizeof(T) == 4, "FP64 takes the general path (vel_cell)");
   using Sh = AffShape<T, NP, NQ, NQY>;
   constexpr int NP3 = Sh::NP3, NPTS = Sh::NPTS;
   __shared__ T s_r0[3 * NP3];
@@ -1499,34 +1494,18 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
 
   const int ex = b % M.nx;
   const int t0 = b / M.nx;
-  int ey, ez;
-  int64_t enr = -1;
-  if (ENR) {
-    const int slot = t0 % M.nslots;
-    ez = t0 / M.nslots;
-    ey = (slot == M.lower_slot) ? 0 : M.ny - 1;
-    enr = b;
-  } else {
-    ey = layer_lo + t0 % nlayers;
-    ez = t0 / nlayers;
-  }
+  const int slot = t0 % M.nslots, ez = t0 / M.nslots, ey = (slot == M.lower_slot) ? 0 : M.ny - 1;
+  const int64_t enr = b;
   const int64_t e = ex + (int64_t)M.nx * (ey + (int64_t)M.ny * ez);
   const T hx = T(M.hx), hz = T(M.hz), hy = T(M.hy[ey]);
   const T ix = T(M.ihx), iy = T(M.ihy[ey]), iz = T(M.ihz);
 
-  const double* tab = M.tab;
   using Sx = ct::MatS<NP, NQ>;
   using Sy = ct::MatS<NP, NQY>;
   using Dx = ct::MatD<NP, NQ>;
   using Dy = ct::MatD<NP, NQY>;
   constexpr auto& tbx = ct::tab<NP, NQ>;
   constexpr auto& tby = ct::tab<NP, NQY>;
-  constexpr bool MEM = sizeof(T) == 8;
-  constexpr TabLayout TL = tab_layout(NP, NQ, NQY);
-  const double* mSx = tab + TL.S;
-  const double* mDx = tab + TL.D;
-  const double* mSy = tab + (ENR ? TL.Sy : TL.S);
-  const double* mDy = tab + (ENR ? TL.Dy : TL.D);
 
   T* s_u = s_r0;
   T* s_val = s_vol;             // [c][pt]
@@ -1535,10 +1514,10 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
   T* tB = tA + Sh::TA;          // (NQ, NQY, NP) x 3
   T* s_nl = Sh::NL_EARLY ? tB + Sh::TB : s_grad;
   for (int i = tid; i < 3 * NP3; i += nt) s_u[i] = u[e * 3 * NP3 + i];
-  if (ENR && tid < 3) s_ut[tid] = u[M.enr_off + enr * 3 + tid];
+  if (tid < 3) s_ut[tid] = u[M.enr_off + enr * 3 + tid];
   NbLines<T, NP> nbl;
   nb_fetch<T, NP>(M, u, ex, ey, ez, nbl);
-  load_face_tab<T, NP, NQ, NQY, ENR>(tab, s_tab);
+  load_face_tab<T, NP, NQ, NQY, true>(M.tab, s_tab);
   if (tid < 32) {
     const int rule = tid >> 4, side = (tid >> 3) & 1, q = tid & 7;
     double v = 0.0;
@@ -1567,11 +1546,11 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
 
   // values at the Gauss points: x, y, z interpolation sweeps; the
   // neighbours' node layers go to LDS with the last one (or right after it)
-  sweep_c<0, NP, NP, NP, NQ, false, false, Sx, 256, MEM>(s_u, NP3, tA, NQ * NP * NP, T(1), 3, 0, mSx);
+  sweep_c<0, NP, NP, NP, NQ, false, false, Sx>(s_u, NP3, tA, NQ * NP * NP, T(1), 3, 0);
   __syncthreads();
-  sweep_c<1, NQ, NP, NP, NQY, false, false, Sy, 256, MEM>(tA, NQ * NP * NP, tB, NQ * NQY * NP, T(1), 3, 0, mSy);
+  sweep_c<1, NQ, NP, NP, NQY, false, false, Sy>(tA, NQ * NP * NP, tB, NQ * NQY * NP, T(1), 3, 0);
   __syncthreads();
-  sweep_c<2, NQ, NQY, NP, NQ, false, false, Sx, 256, MEM>(tB, NQ * NQY * NP, s_val, NPTS, T(1), 3, 0, mSx);
+  sweep_c<2, NQ, NQY, NP, NQ, false, false, Sx>(tB, NQ * NQY * NP, s_val, NPTS, T(1), 3, 0);
   if (!Sh::NL_EARLY) __syncthreads();
   nb_store<T, NP, NQ, false>(M, nbl, s_nl, s_nut, ex, ey, ez, ix, iz, T(M.ihy[y0]), T(M.ihy[y1]));
   __syncthreads();
@@ -1586,26 +1565,26 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
   // gradients by collocation through the Gauss points (over the layers)
   constexpr int NLG = 3 * NPTS / NQ;
   constexpr int NLY = 3 * NPTS / NQY;
-  sweep_c<0, NQ, NQY, NQ, NQ, false, false, Dx, 256, MEM>(s_val, NPTS, s_grad + 0 * NPTS, 3 * NPTS, ix, 3, 0, mDx);
-  sweep_c<1, NQ, NQY, NQ, NQY, false, false, Dy, 256, MEM>(s_val, NPTS, s_grad + 1 * NPTS, 3 * NPTS, iy, 3,
-                                                           NLG % 256, mDy);
-  sweep_c<2, NQ, NQY, NQ, NQ, false, false, Dx, 256, MEM>(s_val, NPTS, s_grad + 2 * NPTS, 3 * NPTS, iz, 3,
-                                                          (NLG + NLY) % 256, mDx);
+  sweep_c<0, NQ, NQY, NQ, NQ, false, false, Dx>(s_val, NPTS, s_grad + 0 * NPTS, 3 * NPTS, ix, 3, 0);
+  sweep_c<1, NQ, NQY, NQ, NQY, false, false, Dy>(s_val, NPTS, s_grad + 1 * NPTS, 3 * NPTS, iy, 3,
+                                                           NLG % 256);
+  sweep_c<2, NQ, NQY, NQ, NQ, false, false, Dx>(s_val, NPTS, s_grad + 2 * NPTS, 3 * NPTS, iz, 3,
+                                                          (NLG + NLY) % 256);
   __syncthreads();
 
   // numerical fluxes of all six faces (in place; one face per wavefront)
   T rt[3] = {0, 0, 0};
-  aff_flux<T, NP, NQ, NQY, ENR, 0, 0>(M, s_val, s_grad, FL, s_ut, s_nut, nb[0].wall, nb[0].enr_nb, tau[0], enr, hy,
+  aff_flux<T, NP, NQ, NQY, 0, 0>(M, s_val, s_grad, FL, s_ut, s_nut, nb[0].wall, nb[0].enr_nb, tau[0], enr, hy,
                                       hz, rt, 0);
-  aff_flux<T, NP, NQ, NQY, ENR, 0, 1>(M, s_val, s_grad, FL, s_ut, s_nut, nb[1].wall, nb[1].enr_nb, tau[1], enr, hy,
+  aff_flux<T, NP, NQ, NQY, 0, 1>(M, s_val, s_grad, FL, s_ut, s_nut, nb[1].wall, nb[1].enr_nb, tau[1], enr, hy,
                                       hz, rt, 64);
-  aff_flux<T, NP, NQ, NQY, ENR, 1, 0>(M, s_val, s_grad, FL, s_ut, s_nut, nb[2].wall, nb[2].enr_nb, tau[2], enr, hx,
+  aff_flux<T, NP, NQ, NQY, 1, 0>(M, s_val, s_grad, FL, s_ut, s_nut, nb[2].wall, nb[2].enr_nb, tau[2], enr, hx,
                                       hz, rt, 128);
-  aff_flux<T, NP, NQ, NQY, ENR, 1, 1>(M, s_val, s_grad, FL, s_ut, s_nut, nb[3].wall, nb[3].enr_nb, tau[3], enr, hx,
+  aff_flux<T, NP, NQ, NQY, 1, 1>(M, s_val, s_grad, FL, s_ut, s_nut, nb[3].wall, nb[3].enr_nb, tau[3], enr, hx,
                                       hz, rt, 192);
-  aff_flux<T, NP, NQ, NQY, ENR, 2, 0>(M, s_val, s_grad, FL, s_ut, s_nut, nb[4].wall, nb[4].enr_nb, tau[4], enr, hx,
+  aff_flux<T, NP, NQ, NQY, 2, 0>(M, s_val, s_grad, FL, s_ut, s_nut, nb[4].wall, nb[4].enr_nb, tau[4], enr, hx,
                                       hy, rt, 128);
-  aff_flux<T, NP, NQ, NQY, ENR, 2, 1>(M, s_val, s_grad, FL, s_ut, s_nut, nb[5].wall, nb[5].enr_nb, tau[5], enr, hx,
+  aff_flux<T, NP, NQ, NQY, 2, 1>(M, s_val, s_grad, FL, s_ut, s_nut, nb[5].wall, nb[5].enr_nb, tau[5], enr, hx,
                                       hy, rt, 192);
   __syncthreads();
 
@@ -1623,19 +1602,13 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
 #pragma unroll
       for (int d = 0; d < 3; ++d) gg[c][d] = s_grad[(c * 3 + d) * NPTS + pt];
     }
-    T gps[3] = {0, 0, 0};
-    if (ENR) {
-      const double* ps = M.psi + ((size_t)enr * M.psi_pts + pt) * 4;
-      const T psv = T(ps[0]);
-      gps[0] = T(ps[1]);
-      gps[1] = T(ps[2]);
-      gps[2] = T(ps[3]);
+    const double* ps = M.psi + ((size_t)enr * M.psi_pts + pt) * 4;
+    const T psv = T(ps[0]), gps[3] = {T(ps[1]), T(ps[2]), T(ps[3])};
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        uu[c] += psv * s_ut[c];
+    for (int c = 0; c < 3; ++c) {
+      uu[c] += psv * s_ut[c];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) gg[c][d] += s_ut[c] * gps[d];
-      }
+      for (int d = 0; d < 3; ++d) gg[c][d] += s_ut[c] * gps[d];
     }
     T G[3][3];
 #pragma unroll
@@ -1643,7 +1616,7 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         G[c][d] = wq * (nu * (gg[c][d] + gg[d][c]) - uu[c] * uu[d]);
-        if (ENR) rt[c] += G[c][d] * gps[d];
+        rt[c] += G[c][d] * gps[d];
       }
     T V[3] = {0, 0, 0};
     aff_spread<T, NQ, NQY, 0, 0>(FL, s_ext, qx, qy, qz, V, G);
@@ -1662,8 +1635,8 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
   __syncthreads();
 
   // integrate: W = sum_d D_d^T G_d / h_d + V, then transposed interpolation
-  sweep_c_inplace<0, NQ, NQY, NQ, true, Dx, 256, MEM>(s_grad + 0 * NPTS, 3 * NPTS, ix, 3, 0, mDx);
-  sweep_c_inplace<1, NQ, NQY, NQ, true, Dy, 256, MEM>(s_grad + 1 * NPTS, 3 * NPTS, iy, 3, NLG % 256, mDy);
+  sweep_c_inplace<0, NQ, NQY, NQ, true, Dx>(s_grad + 0 * NPTS, 3 * NPTS, ix, 3, 0);
+  sweep_c_inplace<1, NQ, NQY, NQ, true, Dy>(s_grad + 1 * NPTS, 3 * NPTS, iy, 3, NLG % 256);
   __syncthreads();
   {
     T* tB2 = s_fl;                        // (NQ, NQY, NP) x 3
@@ -1683,7 +1656,7 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
       for (int m = 0; m < NQ; ++m) {
         T sacc = 0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) sacc += T(MEM ? mDx[q * NQ + m] : tbx.D[q][m]) * g[q];
+        for (int q = 0; q < NQ; ++q) sacc += T(tbx.D[q][m]) * g[q];
         w[m] += iz * sacc;
       }
       T* o = tB2 + c * (NQ * NQY * NP) + pq;
@@ -1691,22 +1664,20 @@ __device__ __forceinline__ void vel_cell_affine(const MeshDev& M, const T* __res
       for (int i = 0; i < NP; ++i) {
         T sacc = 0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) sacc += T(MEM ? mSx[q * NP + i] : tbx.S[q][i]) * w[q];
+        for (int q = 0; q < NQ; ++q) sacc += T(tbx.S[q][i]) * w[q];
         o[i * NQ * NQY] = sacc;
       }
     }
     __syncthreads();
-    sweep_c<1, NQ, NQY, NP, NP, true, false, Sy, 256, MEM>(tB2, NQ * NQY * NP, tA2, NQ * NP * NP, T(1), 3, 0, mSy);
+    sweep_c<1, NQ, NQY, NP, NP, true, false, Sy>(tB2, NQ * NQY * NP, tA2, NQ * NP * NP, T(1), 3, 0);
     __syncthreads();
     T* s_r = s_r0;
-    sweep_c<0, NQ, NP, NP, NP, true, false, Sx, 256, MEM>(tA2, NQ * NP * NP, s_r, NP3, T(1), 3, 0, mSx);
+    sweep_c<0, NQ, NP, NP, NP, true, false, Sx>(tA2, NQ * NP * NP, s_r, NP3, T(1), 3, 0);
     __syncthreads();
     for (int i = tid; i < 3 * NP3; i += nt) r[e * 3 * NP3 + i] = s_r[i];
   }
-  if (ENR) {
-    block_sum3(rt, s_red);
-    if (tid < 3) r[M.enr_off + enr * 3 + tid] = rt[0];
-  }
+  block_sum3(rt, s_red);
+  if (tid < 3) r[M.enr_off + enr * 3 + tid] = rt[0];
 }
 
 // One cell: block-local index b within its launch (regular cells: the layers
@@ -1715,6 +1686,7 @@ template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, bool MS = 
 __device__ __forceinline__ void vel_cell_general(const MeshDev& M, const T* __restrict__ u, T* __restrict__ r, int b,
                                                  int layer_lo, int nlayers, int layer_step = 1) {
   static_assert(LE == 1 || (LE == 8 && !CURVED), "degree-1 weights: flat cells");
+  static_assert(ENR || CURVED || LE != 1, "other flat cells: launch_residual_regular, launch_viscous_regular");
   using Sh = VelShape<T, NP, NQ, NQY>;
   constexpr int NP3 = Sh::NP3, NPTS = Sh::NPTS;
   __shared__ T s_u[3 * NP3];
@@ -2045,16 +2017,14 @@ __host__ __device__ constexpr bool vel_use_affine() { return sizeof(T) == 4; }
 
 // Workgroups per CU the launch bounds plan for: the folded-face path is
 // limited by its LDS, the general path by registers.
-// (FP64 enriched cells keep up to 256 registers, other FP64 cells 168, FP32
-// cells 128: below that they spill.)
+// (FP64 cells keep up to 168 registers, FP32 cells 128: below that they spill.)
 template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, int LE = 1>
 __host__ __device__ constexpr int vel_wg_per_cu() {
   if (CURVED) return sizeof(T) == 8 ? 2 : 4;  // as many as the LDS holds at k = 5
   if (LE != 1) return ENR ? 2 : 3;  // general path; enriched cells hold 24 test-row sums
   if (!vel_use_affine<T>() || !AffShape<T, NP, NQ, NQY>::fits) return 3;
   const int by_lds = (160 * 1024) / AffShape<T, NP, NQ, NQY>::BYTES;
-  const int by_regs = sizeof(T) == 8 ? (ENR ? 2 : 3) : 4;
-  return by_lds < by_regs ? by_lds : by_regs;
+  return by_lds < 4 ? by_lds : 4;
 }
 
 // Cells that kern_residual.hip does not take: enriched cells, curved cells and,
@@ -2069,7 +2039,7 @@ template <typename T, int NP, int NQ, int NQY, bool ENR, bool CURVED, int LE = 1
 __device__ __forceinline__ void vel_cell(const MeshDev& M, const T* __restrict__ u, T* __restrict__ r, int b,
                                          int layer_lo, int nlayers, int layer_step = 1) {
   if constexpr (!CURVED && LE == 1 && vel_use_affine<T>() && AffShape<T, NP, NQ, NQY>::fits)
-    vel_cell_affine<T, NP, NQ, NQY, ENR>(M, u, r, b, layer_lo, nlayers);
+    vel_cell_affine<T, NP, NQ, NQY>(M, u, r, b);
   else
     vel_cell_general<T, NP, NQ, NQY, ENR, CURVED, false, LE>(M, u, r, b, layer_lo, nlayers, layer_step);
 }
