@@ -7,6 +7,7 @@
 #include <algorithm>
 
 #include "batch.h"
+#include "ip_line.h"
 
 namespace dgwm {
 
@@ -22,31 +23,10 @@ struct SepShape {
   static constexpr int JP = 12 * NP2;                        // tangential jumps [D][2][side][NP2]
 };
 
-// What a cell's line along D meets at its two ends: the neighbours' values
-// and normal derivatives, what an enriched neighbour's psi u~ adds to its
-// value in the jump, the penalties, and walls.
-template <typename T>
-struct Ends {
-  T v[2], d[2], tau[2], ps[2];
-  bool wall[2];
-};
-
-// Viscous interior-penalty operator (adjoint sign theta) of a cell and its six
-// neighbours in nodal form (an enriched neighbour's psi u~ enters the jumps
-// only, as on the interface faces of eq. viscous_multiscale, projected onto
-// the face basis),
-//   V u = nu |J| (M x M x M) R,   R_c = sum_D Q_D u_c + ih_c Dn_c (sum_{d != c} W_d) + sum_s l_s Y_{c,s},
-// with the mass matrix M taken out of every term so that one array per
-// component collects them all:
-//   Q_D u_c   the scalar interior-penalty operator along D (gradient terms
-//             twice for D = c), M^{-1} applied along D;
-//   W_d       = ih_d M^{-1} (int N_i' u_d - sum_faces sg N_i {u_d}), the
-//             central weak derivative of u_d along its own direction; its
-//             nodal derivative along c gives (grad phi_c)_d (grad u)^T_{cd} and
-//             the tangential part of {{2 nu eps(u)}} n on the faces normal to d;
-//   Y_{c,s}   the adjoint term of the faces normal to c, tested with the
-//             tangential derivatives: -theta/2 sg sum_d ih_d E_d [u_d], on the
-//             face plane and lifted by l_s = M^{-1} N(s).
+// Viscous interior-penalty operator (adjoint sign -1) of a cell and its six
+// neighbours in the nodal form of ip_line.h (an enriched neighbour's psi u~
+// enters the jumps only, as on the interface faces of eq. viscous_multiscale,
+// projected onto the face basis).
 // A thread owns one line of nodes of one component along each direction in
 // turn (3 (k+1)^2 threads a cell).  Every value is read and written by whole
 // lines, coefficients come as wide scalar loads from the mesh's tables.
@@ -56,79 +36,56 @@ struct Ends {
 // inverse mass another 72 us; about 70 FMAs per unknown, so what bounds it are
 // the seven reads of u (own cell and six neighbours, mostly from L2) and the
 // barriers between the six phases.
-template <typename T, int NP, int NQ, bool MINV>
-__device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T theta, const T* __restrict__ u,
-                                              T* __restrict__ r, int first, int ncells, int layer_lo, int nlayers) {
+// (A function of its own under the kernel: there the compiler knows that u and
+// r are apart also for the scalar loads; 0.6 us a launch.)
+template <int NP, int NQ, bool MINV>
+__device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, const double* __restrict__ u,
+                                              double* __restrict__ r, int first, int ncells, int layer_lo,
+                                              int nlayers) {
   using Sh = SepShape<NP>;
   constexpr int NP2 = Sh::NP2, NP3 = Sh::NP3, CB = Sh::CB;
   constexpr LinOps O = lin_ops(NP);
-  __shared__ T s_u[CB * 3 * Sh::SC];
-  __shared__ T s_w[CB * 3 * Sh::SC];
-  __shared__ T s_r[CB * 3 * Sh::SC];
-  __shared__ T s_j[CB * Sh::JP];
-  __shared__ T s_e[NP2];
-  const double* const ops_at = M.tab + lin_off + (sizeof(T) == 8 ? 0 : O.f32);
-  ConstTab<T> ops = const_tab<T>(ops_at);
+  __shared__ double s_u[CB * 3 * Sh::SC];
+  __shared__ double s_w[CB * 3 * Sh::SC];
+  __shared__ double s_r[CB * 3 * Sh::SC];
+  __shared__ double s_j[CB * Sh::JP];
+  __shared__ double s_e[NP2];
+  const double* const ops_at = M.tab + lin_off;
+  ConstTab<double> ops = const_tab<double>(ops_at);
   auto phase = [&]() __attribute__((always_inline)) {  // (see const_tab)
     __syncthreads();
-    ops = const_tab<T>(ops_at);
+    ops = const_tab<double>(ops_at);
   };
+  constexpr double theta = -1.0;
   const int tid = threadIdx.x;
   const int cell = tid / Sh::TPC, t = tid - cell * Sh::TPC;
   const int c = t / NP2, k = t - c * NP2;
   const int a = k % NP, b = k / NP;
   const bool live = cell < CB && first + cell < ncells;
-  T* su = s_u + cell * 3 * Sh::SC;
-  T* sw = s_w + cell * 3 * Sh::SC;
-  T* sr = s_r + cell * 3 * Sh::SC;
-  T* sj = s_j + cell * Sh::JP;
+  double* su = s_u + cell * 3 * Sh::SC;
+  double* sw = s_w + cell * 3 * Sh::SC;
+  double* sr = s_r + cell * 3 * Sh::SC;
+  double* sj = s_j + cell * Sh::JP;
   if (tid < NP2) s_e[tid] = ops[O.E + tid];
 
   int e = 0;
-  T ih[3] = {0, 0, 0};
-  Ends<T> en[3];
-  T x[NP], qz[NP];
+  double ih[3] = {0, 0, 0};
+  IpEnds<double> en[3];
+  double vn[3][2];  // the neighbours' values without psi u~
+  double x[NP], qz[NP];
   // the scalar operator on a line, its jumps and (D = c) its weak derivative
-  auto line = [&](int D, const T (&p)[NP], const Ends<T>& n, T (&q)[NP]) __attribute__((always_inline)) {
-    const T rd = ih[D], kap = c == D ? T(2) : T(1);
-    T d0 = 0, d1 = 0;
-#pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      d0 += ops[O.nd0 + l] * p[l];
-      d1 += ops[O.nd1 + l] * p[l];
-    }
-    d0 *= rd;
-    d1 *= rd;
-    // mirror states on a wall: u+ = -u-, grad u+ = grad u-
-    const T J0 = p[0] - (n.wall[0] ? -p[0] : n.v[0] + n.ps[0]);
-    const T J1 = p[NP - 1] - (n.wall[1] ? -p[NP - 1] : n.v[1] + n.ps[1]);
-    const T s0 = d0 + (n.wall[0] ? d0 : n.d[0]), s1 = d1 + (n.wall[1] ? d1 : n.d[1]);
-    const T G0 = rd * (T(0.5) * kap * s0 + n.tau[0] * J0), G1 = rd * (n.tau[1] * J1 - T(0.5) * kap * s1);
-    const T r2 = kap * rd * rd, H0 = T(0.5) * theta * r2 * J0, H1 = -T(0.5) * theta * r2 * J1;
-#pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T acc = 0;
-#pragma unroll
-      for (int m = 0; m < NP; ++m) acc += ops[O.A + l * NP + m] * p[m];
-      q[l] = r2 * acc + ops[O.l0 + l] * G0 + ops[O.l1 + l] * G1 + ops[O.g0 + l] * H0 + ops[O.g1 + l] * H1;
-    }
+  auto line = [&](int D, const double (&p)[NP], const IpEnds<double>& n, const double (&vn)[2],
+                  double (&q)[NP]) __attribute__((always_inline)) {
+    double J[2];
+    ip_line(ops, c == D, ih[D], theta, n, p, q, J, [](double (&)[2]) {});
     if (c == D) {
-      const T a0 = T(0.5) * (p[0] + (n.wall[0] ? p[0] : n.v[0]));
-      const T a1 = T(0.5) * (p[NP - 1] + (n.wall[1] ? p[NP - 1] : n.v[1]));
       int wb, ws;
       NodeLds<NP>::line(D, a, b, wb, ws);
-      T* o = sw + c * Sh::SC + wb;
-#pragma unroll
-      for (int l = 0; l < NP; ++l) {
-        T acc = ops[O.l0 + l] * a0 - ops[O.l1 + l] * a1;
-#pragma unroll
-        for (int m = 0; m < NP; ++m) acc += ops[O.E + l * NP + m] * p[m];
-        o[l * ws] = rd * acc;
-      }
+      ip_weak(ops, ih[D], n.wall[0], n.wall[1], vn[0], vn[1], p, sw + c * Sh::SC + wb, ws);
     } else {
-      T* o = sj + (D * 2 + (c < D ? c : c - 1)) * 2 * NP2 + k;
-      o[0] = J0;
-      o[NP2] = J1;
+      double* o = sj + (D * 2 + (c < D ? c : c - 1)) * 2 * NP2 + k;
+      o[0] = J[0];
+      o[NP2] = J[1];
     }
   };
   if (live) {
@@ -136,13 +93,13 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
     const int ex = i % M.nx, t0 = i / M.nx;
     const int ey = layer_lo + t0 % nlayers, ez = t0 / nlayers;
     e = ex + M.nx * (ey + M.ny * ez);
-    ih[0] = T(M.ihx);
-    ih[1] = T(M.ihy[ey]);
-    ih[2] = T(M.ihz);
-    const T* uc = u + ((int64_t)e * 3 + c) * NP3;
+    ih[0] = M.ihx;
+    ih[1] = M.ihy[ey];
+    ih[2] = M.ihz;
+    const double* uc = u + ((int64_t)e * 3 + c) * NP3;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = uc[NP * k + l];
-    const T pen = T(M.pen);
+    const double pen = M.pen;
 #pragma unroll
     for (int D = 0; D < 3; ++D) {
       int vb, vs;
@@ -150,37 +107,37 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
 #pragma unroll
       for (int S = 0; S < 2; ++S) {
         const int nb = cell_nb(M, e, ex, ey, ez, D, S);
-        T rn = ih[D], v = 0, d = 0;
+        double rn = ih[D], v = 0, d = 0;
         if (nb >= 0) {
-          const T* pn = u + ((int64_t)nb * 3 + c) * NP3 + vb;
+          const double* pn = u + ((int64_t)nb * 3 + c) * NP3 + vb;
           // the neighbour below (S = 0) meets the cell at its xi_D = 1, the one above at its xi_D = 0
           const int nd = S ? O.nd0 : O.nd1;
 #pragma unroll
           for (int l = 0; l < NP; ++l) {
-            const T y = pn[l * vs];
+            const double y = pn[l * vs];
             d += ops[nd + l] * y;
             if (l == (S ? 0 : NP - 1)) v = y;
           }
-          if (D == 1) rn = T(M.ihy[S ? (ey + 1 == M.ny ? 0 : ey + 1) : (ey == 0 ? M.ny - 1 : ey - 1)]);
+          if (D == 1) rn = M.ihy[S ? (ey + 1 == M.ny ? 0 : ey + 1) : (ey == 0 ? M.ny - 1 : ey - 1)];
           d *= rn;
         }
-        T ps = 0;
+        double ps = 0;
         if (D == 1 && nb >= 0) {
           const int k1 = (int)enr_index(M, ex, S ? (ey + 1 == M.ny ? 0 : ey + 1) : (ey == 0 ? M.ny - 1 : ey - 1), ez);
           if (k1 >= 0)
-            ps = T(psi_face_node<NP, NQ>(M, k1, 2 + (1 - S), a, b)) * u[M.enr_off + (int64_t)k1 * 3 + c];
+            ps = psi_face_node<NP, NQ>(M, k1, 2 + (1 - S), a, b) * u[M.enr_off + (int64_t)k1 * 3 + c];
         }
-        en[D].ps[S] = ps;
         en[D].wall[S] = nb < 0;
-        en[D].v[S] = v;
+        en[D].v[S] = D == 1 ? v + ps : v;
+        vn[D][S] = v;
         en[D].d[S] = d;
-        en[D].tau[S] = nb < 0 ? T(M.pen * M.wall_mult) * ih[D] : pen * (rn > ih[D] ? rn : ih[D]);
+        en[D].tau[S] = nb < 0 ? M.pen * M.wall_mult * ih[D] : pen * (rn > ih[D] ? rn : ih[D]);
       }
     }
-    T q[NP];
-    line(0, x, en[0], q);
-    T* o = su + c * Sh::SC + Sh::SJ * k;  // line (a, b) along x starts at SJ a + SK b = SJ k
-    T* ro = sr + c * Sh::SC + Sh::SJ * k;
+    double q[NP];
+    line(0, x, en[0], vn[0], q);
+    double* o = su + c * Sh::SC + Sh::SJ * k;  // line (a, b) along x starts at SJ a + SK b = SJ k
+    double* ro = sr + c * Sh::SC + Sh::SJ * k;
 #pragma unroll
     for (int l = 0; l < NP; ++l) {
       o[l] = x[l];
@@ -191,12 +148,12 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
 
   if (live) {
     int lb, ls;
-    T q[NP];
+    double q[NP];
     NodeLds<NP>::line(1, a, b, lb, ls);
-    T* p = su + c * Sh::SC + lb;
+    double* p = su + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
-    line(1, x, en[1], q);
+    line(1, x, en[1], vn[1], q);
     p = sr + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) p[l * ls] += q[l];
@@ -204,7 +161,7 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
     p = su + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
-    line(2, x, en[2], qz);
+    line(2, x, en[2], vn[2], qz);
   }
   phase();
 
@@ -213,52 +170,28 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
     const int d1 = c == 0 ? 1 : 0, d2 = c == 2 ? 1 : 2;  // the tangential directions, d1 along a, d2 along b
     int lb, ls;
     NodeLds<NP>::line(c, a, b, lb, ls);
-    const T* w1 = sw + d1 * Sh::SC + lb;
-    const T* w2 = sw + d2 * Sh::SC + lb;
+    const double* w1 = sw + d1 * Sh::SC + lb;
+    const double* w2 = sw + d2 * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = w1[l * ls] + w2[l * ls];
-    const T ihc = c == 0 ? ih[0] : (c == 1 ? ih[1] : ih[2]);
-    const T ih1 = c == 0 ? ih[1] : ih[0], ih2 = c == 2 ? ih[1] : ih[2];
-    T y[2];
-    const T* j1 = sj + (c * 2) * 2 * NP2;      // jumps of component d1, then of d2, [side][NP2]
-    const T* j2 = j1 + 2 * NP2;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      T s1 = 0, s2 = 0;
-#pragma unroll
-      for (int j = 0; j < NP; ++j) {
-        s1 += s_e[a * NP + j] * j1[s * NP2 + j + NP * b];
-        s2 += s_e[b * NP + j] * j2[s * NP2 + a + NP * j];
-      }
-      y[s] = (s ? -T(0.5) : T(0.5)) * theta * ihc * (ih1 * s1 + ih2 * s2);
-    }
-    T* p = sr + c * Sh::SC + lb;
-#pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T acc = 0;
-#pragma unroll
-      for (int m = 0; m < NP; ++m) acc += ops[O.Dn + l * NP + m] * x[m];
-      p[l * ls] += ihc * acc + ops[O.l0 + l] * y[0] + ops[O.l1 + l] * y[1];
-    }
+    const double ihc = c == 0 ? ih[0] : (c == 1 ? ih[1] : ih[2]);
+    const double ih1 = c == 0 ? ih[1] : ih[0], ih2 = c == 2 ? ih[1] : ih[2];
+    const double* j1 = sj + (c * 2) * 2 * NP2;      // jumps of component d1, then of d2, [side][NP2]
+    ip_cross(ops, s_e, theta, ihc, ih1, ih2, a, b, j1, j1 + 2 * NP2, x, sr + c * Sh::SC + lb, ls);
   }
   phase();
 
-  const T nu = T(M.nu);
   if (live) {  // along z: add the z part; mass matrix
     int lb, ls;
     NodeLds<NP>::line(2, a, b, lb, ls);
-    T* p = sr + c * Sh::SC + lb;
+    double* p = sr + c * Sh::SC + lb;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls] + qz[l];
+    if (MINV) {
 #pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T acc = 0;
-      if (MINV) acc = x[l];
-      else {
-#pragma unroll
-        for (int m = 0; m < NP; ++m) acc += ops[O.M + l * NP + m] * x[m];
-      }
-      p[l * ls] = acc;
+      for (int l = 0; l < NP; ++l) p[l * ls] = x[l];
+    } else {
+      ip_mass(ops, x, p, ls);
     }
   }
   phase();
@@ -266,34 +199,24 @@ __device__ __forceinline__ void viscous_cells(const MeshDev& M, int lin_off, T t
     if (live) {
       int lb, ls;
       NodeLds<NP>::line(1, a, b, lb, ls);
-      T* p = sr + c * Sh::SC + lb;
+      double* p = sr + c * Sh::SC + lb;
 #pragma unroll
       for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
-#pragma unroll
-      for (int l = 0; l < NP; ++l) {
-        T acc = 0;
-#pragma unroll
-        for (int m = 0; m < NP; ++m) acc += ops[O.M + l * NP + m] * x[m];
-        p[l * ls] = acc;
-      }
+      ip_mass(ops, x, p, ls);
     }
     phase();
   }
   if (live) {
-    const T* p = sr + c * Sh::SC + Sh::SJ * k;
-    T* o = r + ((int64_t)e * 3 + c) * NP3 + NP * k;
+    const double* p = sr + c * Sh::SC + Sh::SJ * k;
+    double* o = r + ((int64_t)e * 3 + c) * NP3 + NP * k;
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l];
-    const T sc = MINV ? nu : nu / (ih[0] * ih[1] * ih[2]);
+    const double sc = MINV ? M.nu : M.nu / (ih[0] * ih[1] * ih[2]);
+    if (MINV) {
 #pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T acc = 0;
-      if (MINV) acc = x[l];
-      else {
-#pragma unroll
-        for (int m = 0; m < NP; ++m) acc += ops[O.M + l * NP + m] * x[m];
-      }
-      o[l] = sc * acc;
+      for (int l = 0; l < NP; ++l) o[l] = sc * x[l];
+    } else {
+      ip_mass(ops, x, o, 1, sc);
     }
   }
 }
@@ -302,8 +225,8 @@ template <int NP, int NQ, bool MINV>
 __global__ __launch_bounds__(256) void viscous_regular_kernel(const MeshDev M, int lin_off,
                                                               const double* __restrict__ u, double* __restrict__ r,
                                                               int ncells, int layer_lo, int nlayers) {
-  viscous_cells<double, NP, NQ, MINV>(M, lin_off, -1.0, u, r, xcd_block(gridDim.x, blockIdx.x) * SepShape<NP>::CB, ncells,
-                                  layer_lo, nlayers);
+  viscous_cells<NP, NQ, MINV>(M, lin_off, u, r, xcd_block(gridDim.x, blockIdx.x) * SepShape<NP>::CB, ncells, layer_lo,
+                              nlayers);
 }
 
 // Vorticity right-hand side b(v) = (v, curl u)_e in nodal form: curl u is a

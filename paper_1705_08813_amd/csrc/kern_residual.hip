@@ -7,14 +7,15 @@
 // one thread; derivatives are taken at the nodes, where
 //   int d_d phi f = Dn_d^T (S x S x S)^T w f   (phi' is in the span of the basis).
 // Viscous terms: linear with constant nu, so they separate exactly into 1-D
-// operators (see viscous_cells in kern_linear.hip for the form); only an
-// enriched neighbour's psi u~ enters by quadrature.
+// operators (ip_line.h); only an enriched neighbour's psi u~ enters the flux by
+// quadrature.
 //
 // 64 x 32 x 32 mesh, k = 4, 61,440 cells: 700 us in FP64 and 390 us in FP32, where
 // the collocation-gradient kernel took 1,224 us and 770 us.  It is bound by the
 // vector unit (some 5,000 instructions a cell, 72% busy) and the eight
 // barriers of a cell; memory would allow 110 us (0.55 GB).
 #include "batch.h"
+#include "ip_line.h"
 #include "velocity.h"
 
 namespace dgwm {
@@ -196,49 +197,32 @@ __device__ __forceinline__ void residual_cells(const MeshDev& M, const T* __rest
   const T theta = T(M.theta);
   T x[NP], qz[NP];
   // the scalar interior-penalty operator of component c along D on one line,
-  // and its jumps for the cross terms (D != c)
+  // and its jumps for the cross terms (D != c); an enriched neighbour's psi u~
+  // enters the adjoint terms here and the flux at the points below
   auto line = [&](int D, const T (&p)[NP], T (&q)[NP]) __attribute__((always_inline)) {
-    const T rd = D == 0 ? VI.ih[0] : (D == 1 ? VI.ih[1] : VI.ih[2]), kap = c == D ? T(2) : T(1);
-    T v[2], dn[2], tau[2];
-    bool wall[2];
+    IpEnds<T> n;
+    const T rd = D == 0 ? VI.ih[0] : (D == 1 ? VI.ih[1] : VI.ih[2]);
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const T* o = vm + Sh::U + ((2 * D + s) * 3 + c) * NP2 + k;
-      v[s] = o[0];
-      dn[s] = o[Sh::NB];
-      wall[s] = VI.nb[2 * D + s] < 0;
+      n.v[s] = o[0];
+      n.d[s] = o[Sh::NB];
+      n.wall[s] = VI.nb[2 * D + s] < 0;
       const T rn = D == 1 && VI.ihn[s] > rd ? VI.ihn[s] : rd;
-      tau[s] = wall[s] ? T(M.pen * M.wall_mult) * rd : T(M.pen) * rn;
+      n.tau[s] = n.wall[s] ? T(M.pen * M.wall_mult) * rd : T(M.pen) * rn;
     }
-    T d0 = 0, d1 = 0;
-#pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      d0 += ops[O.nd0 + l] * p[l];
-      d1 += ops[O.nd1 + l] * p[l];
-    }
-    d0 *= rd;
-    d1 *= rd;
-    // mirror states on a wall: u+ = -u-, grad u+ = grad u-
-    T J0 = p[0] - (wall[0] ? -p[0] : v[0]), J1 = p[NP - 1] - (wall[1] ? -p[NP - 1] : v[1]);
-    const T s0 = d0 + (wall[0] ? d0 : dn[0]), s1 = d1 + (wall[1] ? d1 : dn[1]);
-    const T G0 = rd * (T(0.5) * kap * s0 + tau[0] * J0), G1 = rd * (tau[1] * J1 - T(0.5) * kap * s1);
-    if (D == 1) {  // the adjoint terms also see psi u~ of an enriched neighbour
-      const T* ps = s_psi + vcell * 2 * NP2 + k;
-      if (VI.enr[0] >= 0) J0 -= ps[0] * s_ut[vcell * 6 + c];
-      if (VI.enr[1] >= 0) J1 -= ps[NP2] * s_ut[vcell * 6 + 3 + c];
-    }
-    const T r2 = kap * rd * rd, H0 = T(0.5) * theta * r2 * J0, H1 = -T(0.5) * theta * r2 * J1;
-#pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T acc = 0;
-#pragma unroll
-      for (int m = 0; m < NP; ++m) acc += ops[O.A + l * NP + m] * p[m];
-      q[l] = r2 * acc + ops[O.l0 + l] * G0 + ops[O.l1 + l] * G1 + ops[O.g0 + l] * H0 + ops[O.g1 + l] * H1;
-    }
+    T J[2];
+    ip_line(ops, c == D, rd, theta, n, p, q, J, [&](T (&j)[2]) __attribute__((always_inline)) {
+      if (D == 1) {
+        const T* ps = s_psi + vcell * 2 * NP2 + k;
+        if (VI.enr[0] >= 0) j[0] -= ps[0] * s_ut[vcell * 6 + c];
+        if (VI.enr[1] >= 0) j[1] -= ps[NP2] * s_ut[vcell * 6 + 3 + c];
+      }
+    });
     if (c != D) {
       T* o = vj + (D * 2 + (c < D ? c : c - 1)) * 2 * NP2 + k;
-      o[0] = J0;
-      o[NP2] = J1;
+      o[0] = J[0];
+      o[NP2] = J[1];
     }
   };
   // W_c: the weak derivative of component c along direction c
@@ -249,17 +233,7 @@ __device__ __forceinline__ void residual_cells(const MeshDev& M, const T* __rest
 #pragma unroll
     for (int l = 0; l < NP; ++l) x[l] = p[l * ls];
     const T* o = vm + Sh::U + 7 * c * NP2 + k;  // face 2 c, component c
-    const T a0 = T(0.5) * (x[0] + (VI.nb[2 * c] < 0 ? x[0] : o[0]));
-    const T a1 = T(0.5) * (x[NP - 1] + (VI.nb[2 * c + 1] < 0 ? x[NP - 1] : o[3 * NP2]));
-    const T rd = VI.ih[c];
-    T* w = vw + c * L::SC + lb;
-#pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T acc = ops[O.l0 + l] * a0 - ops[O.l1 + l] * a1;
-#pragma unroll
-      for (int m = 0; m < NP; ++m) acc += ops[O.E + l * NP + m] * x[m];
-      w[l * ls] = rd * acc;
-    }
+    ip_weak(ops, VI.ih[c], VI.nb[2 * c] < 0, VI.nb[2 * c + 1] < 0, o[0], o[3 * NP2], x, vw + c * L::SC + lb, ls);
   };
   auto mass = [&](int D) __attribute__((always_inline)) {  // M along D on this thread's line of the viscous rows
     int lb, ls;
@@ -271,13 +245,7 @@ __device__ __forceinline__ void residual_cells(const MeshDev& M, const T* __rest
 #pragma unroll
       for (int l = 0; l < NP; ++l) x[l] += qz[l];
     }
-#pragma unroll
-    for (int l = 0; l < NP; ++l) {
-      T acc = 0;
-#pragma unroll
-      for (int m = 0; m < NP; ++m) acc += ops[O.M + l * NP + m] * x[m];
-      p[l * ls] = acc;
-    }
+    ip_mass(ops, x, p, ls);
   };
   const int wt = (tid + 128) & 255;  // items of the point phases start at the third wavefront
 
@@ -537,27 +505,9 @@ __device__ __forceinline__ void residual_cells(const MeshDev& M, const T* __rest
       for (int l = 0; l < NP; ++l) y[l] = w1[l * ls] + w2[l * ls];
       const T ihc = cc == 0 ? I.ih[0] : (cc == 1 ? I.ih[1] : I.ih[2]);
       const T ih1 = cc == 0 ? I.ih[1] : I.ih[0], ih2 = cc == 2 ? I.ih[1] : I.ih[2];
-      T yb[2];
       const T* j1 = m + Sh::R1 + Sh::B + Sh::W + (cc * 2) * 2 * NP2;
-      const T* j2 = j1 + 2 * NP2;
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        T a1 = 0, a2 = 0;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-          a1 += s_e[aa * NP + j] * j1[s * NP2 + j + NP * bb];
-          a2 += s_e[bb * NP + j] * j2[s * NP2 + aa + NP * j];
-        }
-        yb[s] = (s ? -T(0.5) : T(0.5)) * theta * ihc * (ih1 * a1 + ih2 * a2);
-      }
-      T* p = m + Sh::R1 + Sh::R2 + Sh::R3 + cc * L::SC + lb;
-#pragma unroll
-      for (int l = 0; l < NP; ++l) {
-        T acc = 0;
-#pragma unroll
-        for (int n = 0; n < NP; ++n) acc += ops[O.Dn + l * NP + n] * y[n];
-        p[l * ls] += ihc * acc + ops[O.l0 + l] * yb[0] + ops[O.l1 + l] * yb[1];
-      }
+      ip_cross(ops, s_e, theta, ihc, ih1, ih2, aa, bb, j1, j1 + 2 * NP2, y, m + Sh::R1 + Sh::R2 + Sh::R3 + cc * L::SC + lb,
+               ls);
     }
   }
   phase();
