@@ -18,8 +18,8 @@
 // 256 unknowns (a CU alone reads the n^2 entries of a larger one slower than
 // the launches cost).  16 x 8 x 8 cells, k = 3: the levels of 16 and 2 cells and
 // the coarsest solve 26 us, 80 us as 17 launches; 1.2 us a step, the latency of
-// its LDS passes, and 11 us around them.  A solve 2.88 -> 2.42 ms; eight solves
-// of 16 x 16 x 16 cells, k = 2, 10.0 -> 8.5 ms.
+// its LDS passes, and 11 us around them.  A solve 2.9 -> 2.5 ms; eight solves
+// of 16 x 16 x 16 cells, k = 2, 10.0 -> 8.3 ms (single runs of either spread by 5%).
 #include <algorithm>
 #include <vector>
 

@@ -764,7 +764,7 @@ __global__ __launch_bounds__(kCoupThreads) void coupling_kernel(const InvMassArg
 // on four columns of a cell, its right-hand side and the three couplings, then
 // the 3 x 3 Schur complement of the enrichment unknowns.  Four cells fill the 16
 // columns of a matrix-core product; only the combined column of each is needed
-// from the second one.  4,096 cells, k = 4: 127 us, 376 us with dense tables.
+// from the second one.  4,096 cells, k = 4: 108 us, 376 us with dense tables.
 template <int NP>
 __global__ __launch_bounds__(tile_threads(NP), tile_waves(NP)) void bordered_step_kernel(const BorderArgs S) {
   constexpr int NP2 = NP * NP, NP3 = NP2 * NP, N = 3 * NP3, LD = kTileLD, NT = tile_threads(NP);

@@ -10,7 +10,7 @@
 // operators (ip_line.h); only an enriched neighbour's psi u~ enters the flux by
 // quadrature.
 //
-// 64 x 32 x 32 mesh, k = 4, 61,440 cells: 700 us in FP64 and 390 us in FP32, where
+// 64 x 32 x 32 mesh, k = 4, 61,440 cells: 680 us in FP64 and 415 us in FP32, where
 // the collocation-gradient kernel took 1,224 us and 770 us.  It is bound by the
 // vector unit (some 5,000 instructions a cell, 72% busy) and the eight
 // barriers of a cell; memory would allow 110 us (0.55 GB).

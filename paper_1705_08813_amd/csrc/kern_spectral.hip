@@ -19,8 +19,8 @@
 // cells of one layer and runs both block products out of LDS on the FP64
 // matrix cores.  The result is exact up to rounding: no iteration, every cell
 // the same work.
-// Measured (64 x 32 x 32 cells, k = 4, 61,440 cells here): 324 us, 0.55 GB at
-// 1.7 TB/s; with the dense 375 x 375 tables it was 1,196 us, bound by their
+// Measured (64 x 32 x 32 cells, k = 4, 61,440 cells here): 305 us, 0.55 GB at
+// 1.8 TB/s; with the dense 375 x 375 tables it was 1,196 us, bound by their
 // products.  What is left is the LDS passes between barriers and, at the FP64
 // matrix rate, 80 us of products.  Eight wavefronts on a tile instead of four
 // fill the wait of one phase with another tile's work at the same LDS.

@@ -833,7 +833,7 @@ __device__ __forceinline__ void vel_faces_dir(const MeshDev& M, const T* s_u, co
 // an LDS read feeds a whole column of a table and the table entries come from
 // scalar registers.  The flux phase has one thread per face point and side; its
 // geometry and psi values are loaded two phases ahead.  48 x 24 x 24 cells, k =
-// 5, FP64: 1,410 us for the cells without enrichment (25,344 of them, 1.8 GB of
+// 5, FP64: 1,320 us for the cells without enrichment (25,344 of them, 1.8 GB of
 // geometry), 1,556 us with a table read from LDS per product.  What is left is
 // the vector unit at 46% behind 26 barriers with two workgroups a CU; padding
 // the point fields against bank conflicts did not shorten it.
