@@ -664,11 +664,11 @@ using MDt = ct::MatSd<NP, NQ>;
 // spectral product together; every C'^T P^{-1} (.) is then a weighted dot
 // product of its outputs, sum_r y_j[r] y_k[r] / (1 + tau lambda_r); and by
 // linearity only x'_p = P^{-1} (b_p - C' x_e) takes the second product.  Four
-// cells per workgroup, one wavefront per cell in the dense products.  A cell
-// whose enrichment is off has x_e = 0 and x_p = P^{-1} b_p.
+// cells per workgroup share both products.  A cell whose enrichment is off
+// has x_e = 0 and x_p = P^{-1} b_p.
 struct BorderArgs {
   InvMassArgs im;
-  const double* mats;   // K^{-1}, C^T, C^{-T}
+  const double* mats;   // K^{-1}
   const double* slots;  // per layer slot: (L Z)^T and L^{-T} Z tables, lambda
   const int32_t* map;
   const double* tau_d;
